@@ -890,8 +890,8 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
         // the vertex positions are no longer needed: their LDS holds the
         // record's scratch (zero-length edge bits, vertex numbers, degrees)
         uint8_t *wsc = reinterpret_cast<uint8_t *>(&sh.u.st.pos[0][0]);
-        const int wl = wb_record<64, S, MAXP>(A.wbg + (int64_t)id * kWbStride, sumord, sh.u.st.tpl, sh.u.st.lab,
-                                              sh.etab, wsc, wsc + 64 * S, wsc + 128 * S, zb, lane, 0);
+        const int wl = wb_record<64, S>(A.wbg + (int64_t)id * kWbStride, sumord, sh.u.st.tpl, sh.u.st.lab,
+                                              TwinByPlanes<MAXP>{sh.etab}, wsc, wsc + 64 * S, wsc + 128 * S, zb, lane, 0);
         if (lane == 0) A.wbl[id] = wl;
     }
     if (lane == 0) {

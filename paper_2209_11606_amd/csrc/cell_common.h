@@ -808,13 +808,29 @@ __device__ __forceinline__ int grp_isum(int v)
     return v;
 }
 
-// slot of the triangle across edge k (planes k, k+1) of slot s
-template <int NT, int MAXP>
-__device__ __forceinline__ int wb_twin(const uint32_t *tpl, const uint8_t (*etab)[MAXP], int s, int k)
+// slot of the triangle across edge k (planes k, k+1) of slot s, from either
+// form of the kernels' edge tables: the slot by directed edge of planes, or
+// the number 4 slot + edge of the twin by edge number
+template <int MAXP>
+struct TwinByPlanes {
+    const uint8_t (*etab)[MAXP];
+    __device__ __forceinline__ int operator()(const uint32_t *tpl, int s, int k) const
+    {
+        const uint32_t t3 = tpl[s];
+        const int a = (t3 >> (8 * k)) & 0xff, b = (t3 >> (8 * (k == 2 ? 0 : k + 1))) & 0xff;
+        return etab[b][a];
+    }
+};
+
+struct TwinNumber {
+    const uint8_t *nb;
+    __device__ __forceinline__ int operator()(const uint32_t *, int s, int k) const { return nb[4 * s + k] >> 2; }
+};
+
+template <int NT, class E>
+__device__ __forceinline__ int wb_twin(const uint32_t *tpl, E tw, int s, int k)
 {
-    const uint32_t t3 = tpl[s];
-    const int a = (t3 >> (8 * k)) & 0xff, b = (t3 >> (8 * (k == 2 ? 0 : k + 1))) & 0xff;
-    return etab[b][a] & (NT - 1);
+    return tw(tpl, s, k) & (NT - 1);
 }
 
 // Once around the vertex that slot r belongs to, starting at r's first
@@ -827,9 +843,9 @@ __device__ __forceinline__ int wb_twin(const uint32_t *tpl, const uint8_t (*etab
 // once: emit(j, w_i) for every i with w_i != w_{i+1} (cyclically).  An edge
 // back into the vertex itself is not an edge of the cell.  Returns the
 // degree, or -1 for an inconsistent graph (or no positive edge at r).
-template <int NT, int MAXP, class F>
-__device__ __forceinline__ int wb_walk(const uint32_t *tpl, const uint8_t (*etab)[MAXP], const uint8_t *zbt,
-                                       const uint8_t *vid, int r, F emit)
+template <int NT, class E, class F>
+__device__ __forceinline__ int wb_walk(const uint32_t *tpl, E etab, const uint8_t *zbt, const uint8_t *vid, int r,
+                                       F emit)
 {
     int k0 = 0;
     while (k0 < 3 && ((zbt[r] >> k0) & 1)) k0++;
@@ -837,7 +853,7 @@ __device__ __forceinline__ int wb_walk(const uint32_t *tpl, const uint8_t (*etab
     const int self = vid[r];
     int s = r, k = k0, n = 0, nraw = 0, first = -1, pend = -1;
     do {
-        const int w = vid[wb_twin<NT, MAXP>(tpl, etab, s, k)];
+        const int w = vid[wb_twin<NT>(tpl, etab, s, k)];
         if (w != self) {
             if (nraw == 0) {
                 first = w;
@@ -852,7 +868,7 @@ __device__ __forceinline__ int wb_walk(const uint32_t *tpl, const uint8_t (*etab
         int guard = 0;
         while ((zbt[s] >> k) & 1) {
             const int b = (tpl[s] >> (8 * (k == 2 ? 0 : k + 1))) & 0xff;
-            const int s2 = wb_twin<NT, MAXP>(tpl, etab, s, k);
+            const int s2 = wb_twin<NT>(tpl, etab, s, k);
             const uint32_t u3 = tpl[s2];
             int k2 = 0;
             while (k2 < 3 && (int)((u3 >> (8 * k2)) & 0xff) != b) k2++;
@@ -875,9 +891,9 @@ __device__ __forceinline__ int wb_walk(const uint32_t *tpl, const uint8_t (*etab
 // degs are LDS scratch of GW * S bytes.  Returns (in every lane) the code
 // length D = 2E, or 0 when the record does not fit or the graph is found
 // inconsistent: no code for the cell.
-template <int GW, int S, int MAXP>
-__device__ __noinline__ int wb_record(uint8_t *rec, int D, const uint32_t *tpl, const int32_t *lab, const uint8_t (*etab)[MAXP],
-                         uint8_t *zbt, uint8_t *vid, uint8_t *degs, uint32_t zb, int gl, int gb)
+template <int GW, int S, class E>
+__device__ __noinline__ int wb_record(uint8_t *rec, int D, const uint32_t *tpl, const int32_t *lab, E etab,
+                                      uint8_t *zbt, uint8_t *vid, uint8_t *degs, uint32_t zb, int gl, int gb)
 {
     constexpr int NT = GW * S;
     int V = 0;
@@ -914,7 +930,7 @@ __device__ __noinline__ int wb_record(uint8_t *rec, int D, const uint32_t *tpl, 
                     r = u;
                     break;
                 }
-        const int dg = wb_walk<NT, MAXP>(tpl, etab, zbt, vid, r, [](int, int) {});
+        const int dg = wb_walk<NT>(tpl, etab, zbt, vid, r, [](int, int) {});
         if (dg < 3) {
             bad = true;
             continue;
@@ -934,7 +950,7 @@ __device__ __noinline__ int wb_record(uint8_t *rec, int D, const uint32_t *tpl, 
         for (int u = 0; u < v; u++) off += degs[u];
         rec[3 + v] = degs[v];
         uint8_t *out = rec + 3 + V + off;
-        wb_walk<NT, MAXP>(tpl, etab, zbt, vid, start[s], [&](int j, int w) { out[j] = (uint8_t)w; });
+        wb_walk<NT>(tpl, etab, zbt, vid, start[s], [&](int j, int w) { out[j] = (uint8_t)w; });
     }
     if (gl == 0) {
         rec[0] = (uint8_t)V;
