@@ -22,10 +22,10 @@
 //
 //   NEW -> GATHER -> BATCH -> TEST -> (CUT -> TEST)* -> ... -> STATS -> NEW
 //
-// GATHER reads the particle counts of up to G blocks, BATCH loads up to G
-// particles, keeps those inside the radius bound and sorts them by distance
-// (a rank count over the group's keys), TEST takes the sorted candidates one
-// at a time, and a conflict parks the group in CUT.  The cut itself (the
+// GATHER reads the particle counts of up to 64 blocks and BATCH loads up to
+// 64 particles, keeps those inside the radius bound and sorts them by distance
+// (a rank count over the keys), both with the whole wave for one cell at a
+// time.  TEST takes the sorted candidates one at a time, and a conflict parks the group in CUT.  The cut itself (the
 // costliest step) runs only once no group of the wave can advance without
 // one, so that the cuts of the wave's cells run in the same instructions
 // instead of one after another.  STATS (volume, centroid, counts, face
@@ -46,6 +46,8 @@ struct Gw {
     static constexpr int CPW = 64 / G;
     static constexpr uint32_t FULL = G >= 32 ? 0xffffffffu : ((1u << G) - 1u);
 };
+
+constexpr int kFirstBlocks = 16;  // blocks of a cell's first gather
 
 enum { PH_NEW, PH_GATHER, PH_BATCH, PH_TEST, PH_CUT, PH_STATS, PH_DONE };
 
@@ -185,17 +187,18 @@ struct SL {
         struct {               // the search
             double cq[G][6];   // the batch's candidates, nearest first: q, plane offset h,
                                // |q|^2 (1 - 2^-14), FP64 side-test band
+            union {
+                alignas(16) uint32_t key[G + 4];  // ranking keys (BATCH only)
+                float cfb[G];                     // then: the FP32 side-test bands (FP32 filter)
+            } x;
             int32_t cid[G];
-            int32_t cpre[G];   // the gather's blocks: candidates before, first particle, image code
-            int32_t cbeg[G];
-            uint16_t csh[G];   // the gather's blocks: image code | shifts + 2 in 3-bit fields << 7
+            int32_t cpre[65];  // the gather's blocks: particles before, first particle less that,
+            int32_t coff[64];  // image code | shifts + 2 in 3-bit fields << 7
+            uint16_t csh[64];
+            uint8_t mark[64];  // BATCH: block of each lane
             uint8_t ccode[G];
             uint32_t bedge[G * S];  // CUT: boundary edges a | b << 8 | number << 16
             uint8_t first[MAXP];    // CUT: 4 x slot of the new triangle whose first plane is a
-            union {
-                uint32_t key[G];            // ranking keys (BATCH only)
-                float cfb[G];               // then: the FP32 side-test bands (FP32 filter)
-            } x;
         } w;
         struct {               // the statistics of the finished cell
             double pos[G * S][3];
@@ -384,154 +387,185 @@ __device__ __forceinline__ void ph_new(const CellArgs &A, SL<G, S, MAXP, RAD> &s
     c.phase = PH_GATHER;
 }
 
-// ---- GATHER: particle counts of the next (up to) G blocks ----
-template <int G, int S, int MAXP, bool F32, bool RAD>
-__device__ __forceinline__ void ph_gather(const CellArgs &A, SL<G, S, MAXP, RAD> &sh, SCell<S, F32> &c, int gl, int gb,
-                                          uint32_t *cnt)
+// The search steps take all 64 lanes for one cell: a wave's cells seldom
+// need particles at the same moment, and a step for one cell costs the wave
+// the same with 64 lanes as with G.  The cell's values are wave-uniform here
+// (its record is read through the scalar cache).  With G lanes a cell of the
+// periodic 10^6 set took 8 batches and 3 gathers, nearly all of them with the
+// other half of the wave idle; with 64, 4,771 -> 4,317 VALU instructions a
+// cell and the step 10.71 -> 9.80 ms (two cells per wave).
+
+// inclusive maximum over the lanes below (values >= 0)
+__device__ __forceinline__ int wave_max_scan(int v)
 {
-    const Tess &T = sh.T;
-    const Grid &G3 = T.G;
-    const double lim = c.lim;
-    int dd[3] = {0, 0, 0};
-    bool v = false;
-    if (sh.gs.cur >= A.noff) {
-        // past the offset list: the shell search of the block bound is the
-        // one-cell kernel's (the spill pass), as for the extended cells below
-        c.phase = -ST_CAP;
-        return;
-    } else if (A.offs[sh.gs.cur].m * 0.25 * T.bsmin2 >= lim) {
-        c.phase = PH_STATS;  // no block left in the offset list can hold a cutting particle
-        return;
-    } else if (sh.gs.cur >= G && lim > 16.0 * T.bsmin2) {
-        // after the nearest blocks the search radius still reaches four
-        // block sides, past most of the offset list: an extended cell
-        // (section 3.1), left to the one-cell kernel of the spill pass,
-        // which tests the list's blocks against the balls and takes 64
-        // blocks of a shell per step
-        c.phase = -ST_CAP;
-        return;
-    } else {
-        int o = sh.gs.cur + gl;
-        v = o < A.noff;
-        Offset of = v ? A.offs[o] : Offset{0, 0, 0, 0};
-        dd[0] = of.dx * sh.gs.fl[0];
-        dd[1] = of.dy * sh.gs.fl[1];
-        dd[2] = of.dz * sh.gs.fl[2];
-        sh.gs.cur += G;
-    }
+    v = max(v, dpp_i32<DPP_ROW_SHR1, 0xf>(0, v));
+    v = max(v, dpp_i32<DPP_ROW_SHR2, 0xf>(0, v));
+    v = max(v, dpp_i32<DPP_ROW_SHR4, 0xf>(0, v));
+    v = max(v, dpp_i32<DPP_ROW_SHR8, 0xf>(0, v));
+    v = max(v, dpp_i32<DPP_ROW_BCAST15, 0xa>(0, v));
+    v = max(v, dpp_i32<DPP_ROW_BCAST31, 0xc>(0, v));
+    return v;
+}
+
+typedef const __attribute__((address_space(4))) Tess *TessConst;
+typedef const __attribute__((address_space(4))) Offset *OffsetConst;
+
+// ---- GATHER: particle counts of the next blocks of the offset list ----
+// The first gather takes kFirstBlocks blocks, whose cuts bring the search
+// radius near its final value; the next ones take 64 and keep those inside it.
+// Returns the next phase.
+template <int G, int S, int MAXP, bool RAD>
+__device__ __forceinline__ int co_gather(const CellArgs &A, SL<G, S, MAXP, RAD> &sh, int lane, double lim)
+{
+    TessConst T = (TessConst)(uintptr_t)(A.tess + __builtin_amdgcn_readfirstlane(sh.gs.tcur));
+    const int cur = __builtin_amdgcn_readfirstlane(sh.gs.cur);
+    // past the offset list: the shell search of the block bound is the
+    // one-cell kernel's (the spill pass), as for the extended cells below
+    if (cur >= A.noff) return -ST_CAP;
+    // no block left in the offset list can hold a cutting particle
+    if (((OffsetConst)(uintptr_t)A.offs)[cur].m * 0.25 * T->bsmin2 >= lim) return PH_STATS;
+    // after the G nearest blocks the search radius still reaches four block
+    // sides, past most of the offset list: an extended cell (section 3.1),
+    // left to the one-cell kernel of the spill pass, which tests the list's
+    // blocks against the balls and takes 64 blocks of a shell per step
+    const bool far = lim > 16.0 * T->bsmin2;
+    if (cur >= G && far) return -ST_CAP;
+    const int width = cur == 0 ? kFirstBlocks : (far ? G - cur : 64);
+    const int o = cur + lane;
+    bool ok = lane < width && o < A.noff;
+    const Offset of = ok ? A.offs[o] : Offset{0, 0, 0, 0};
+    const int dd[3] = {of.dx * sh.gs.fl[0], of.dy * sh.gs.fl[1], of.dz * sh.gs.fl[2]};
     // the blocks: periodic wrap by whole periods (at most two each way), walls
     int bb[3], sv[3];
-    bool ok = v;
     double d2b = 0.0;
 #pragma unroll
     for (int d = 0; d < 3; d++) {
-        const int g = G3.g[d];
-        int t = sh.gs.bc[d] + dd[d];
+        const int g = T->G.g[d];
+        const int t = sh.gs.bc[d] + dd[d];
         int w = t, s = 0;
-        if (G3.per[d]) {
-            while (w < 0 && s > -3) {
-                w += g;
-                s--;
+        if (T->G.per[d]) {
+            if (g >= kOffRadius) {
+                // the list reaches kOffRadius blocks: one period at most
+                s = t < 0 ? -1 : (t >= g ? 1 : 0);
+                w = t - s * g;
+            } else {
+                for (int r = 0; r < 3; r++) {
+                    const int q = w < 0 ? -1 : (w >= g ? 1 : 0);
+                    s += q;
+                    w -= q * g;
+                }
+                if (s > 2 || s < -2 || w < 0 || w >= g) ok = false;
             }
-            while (w >= g && s < 3) {
-                w -= g;
-                s++;
-            }
-            if (s > 2 || s < -2) ok = false;
         } else if (t < 0 || t >= g) {
             ok = false;
         }
         bb[d] = w;
         sv[d] = s;
-        double blo = G3.lo[d] + t * G3.bs[d];
-        double e = fmax(0.0, fmax(blo - sh.gs.p[d], sh.gs.p[d] - (blo + G3.bs[d])));
+        const double blo = T->G.lo[d] + t * T->G.bs[d];
+        const double e = fmax(0.0, fmax(blo - sh.gs.p[d], sh.gs.p[d] - (blo + T->G.bs[d])));
         d2b += e * e;
     }
     if (d2b >= lim) ok = false;
     int cntb = 0, beg = 0;
     if (ok) {
-        int blk = T.bbase + bb[0] + G3.g[0] * (bb[1] + G3.g[1] * bb[2]);
+        const int blk = T->bbase + bb[0] + T->G.g[0] * (bb[1] + T->G.g[1] * bb[2]);
         beg = A.start[blk];
         cntb = A.start[blk + 1] - beg;
     }
-    sh.gs.cnt[DC_BLOCKS] += __popc(gbal<G>(ok, gb));
-    int incl = gscan_incl<G>(cntb);
-    int total = __shfl(incl, gb + G - 1);
+    const int incl = wave_incl_scan(cntb);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    sh.gs.cnt[DC_BLOCKS] += __popcll(__builtin_amdgcn_ballot_w64(ok));
     sh.gs.cnt[DC_LOADED] += total;
-    if (total == 0) return;  // stay in GATHER: next blocks
-    sh.u.w.cpre[gl] = incl - cntb;
-    sh.u.w.cbeg[gl] = beg;
-    sh.u.w.csh[gl] = (uint16_t)((25 * (sv[2] + 2) + 5 * (sv[1] + 2) + (sv[0] + 2)) |
-                                (((sv[0] + 2) | ((sv[1] + 2) << 3) | ((sv[2] + 2) << 6)) << 7));
-    lds_fence();
+    sh.gs.cur = cur + width;
+    if (total == 0) return PH_GATHER;
+    sh.u.w.cpre[lane] = incl - cntb;
+    sh.u.w.cpre[64] = total;
+    sh.u.w.coff[lane] = beg - (incl - cntb);
+    sh.u.w.csh[lane] = (uint16_t)((25 * (sv[2] + 2) + 5 * (sv[1] + 2) + (sv[0] + 2)) |
+                                  (((sv[0] + 2) | ((sv[1] + 2) << 3) | ((sv[2] + 2) << 6)) << 7));
     sh.gs.gtot = total;
     sh.gs.gc0 = 0;
-    c.phase = PH_BATCH;
+    lds_fence();
+    return PH_BATCH;
 }
 
-// ---- BATCH: the next G particles of the gather, sorted by distance ----
+// ---- BATCH: the next particles of the gather, sorted by distance ----
+// 64 particles are loaded; those inside the search radius, at most G, are the
+// batch (when more are inside, as before the first cuts, fewer particles are
+// taken).  Returns the next phase and the size of the batch.
 template <int G, int S, int MAXP, bool F32, bool RAD>
-__device__ __forceinline__ void ph_batch(const CellArgs &A, SL<G, S, MAXP, RAD> &sh, SCell<S, F32> &c, int gl, int gb,
-                                         uint32_t below)
+__device__ __forceinline__ int co_batch(const CellArgs &A, SL<G, S, MAXP, RAD> &sh, int lane, double lim, uint32_t rk,
+                                        int &bn)
 {
-    if (sh.gs.gc0 >= sh.gs.gtot) {
-        c.phase = PH_GATHER;
-        return;
-    }
-    const Grid &G3 = sh.T.G;
-    const int ci = sh.gs.gc0 + gl;
-    uint32_t key = ~0u;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, d2 = 0.0, h = 0.0, rj = 0.0;
+    const int c0 = __builtin_amdgcn_readfirstlane(sh.gs.gc0), tot = __builtin_amdgcn_readfirstlane(sh.gs.gtot);
+    if (c0 >= tot) return PH_GATHER;
+    // the block of each particle: blocks mark the lane of their first one,
+    // and a lane's block is the last mark at or below it
+    const int pre = sh.u.w.cpre[lane], nxt = sh.u.w.cpre[lane + 1];
+    sh.u.w.mark[lane] = 0;
+    lds_fence();
+    if (nxt > pre && nxt > c0 && pre < c0 + 64) sh.u.w.mark[max(pre - c0, 0)] = (uint8_t)(lane + 1);
+    lds_fence();
+    const int b = max(wave_max_scan(sh.u.w.mark[lane]) - 1, 0);
+    const int ci = c0 + lane;
+    bool valid = ci < tot;
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0, d2 = 0.0, h = 0.0;
     int pid = 0, code = 0;
-    if (ci < sh.gs.gtot) {
-        int lo = 0, hi = G - 1;
-        while (lo < hi) {
-            int mid = (lo + hi + 1) >> 1;
-            if (sh.u.w.cpre[mid] <= ci) lo = mid;
-            else hi = mid - 1;
-        }
-        int idx = sh.u.w.cbeg[lo] + (ci - sh.u.w.cpre[lo]);
-        const int cs = sh.u.w.csh[lo];
+    if (valid) {
+        const int idx = sh.u.w.coff[b] + ci;
+        const int cs = sh.u.w.csh[b];
         code = cs & 0x7f;
-        const int s0 = ((cs >> 7) & 7) - 2, s1 = ((cs >> 10) & 7) - 2, s2 = ((cs >> 13) & 7) - 2;
-        Particle q = A.part[idx];
+        const Particle q = A.part[idx];
         a0 = q.x - sh.gs.p[0];
         a1 = q.y - sh.gs.p[1];
         a2 = q.z - sh.gs.p[2];
-        if (s0) a0 = a0 + s0 * G3.L[0];
-        if (s1) a1 = a1 + s1 * G3.L[1];
-        if (s2) a2 = a2 + s2 * G3.L[2];
+        if (code != kNoShift) {
+            const int s0 = ((cs >> 7) & 7) - 2, s1 = ((cs >> 10) & 7) - 2, s2 = ((cs >> 13) & 7) - 2;
+            if (s0) a0 = a0 + s0 * sh.T.G.L[0];
+            if (s1) a1 = a1 + s1 * sh.T.G.L[1];
+            if (s2) a2 = a2 + s2 * sh.T.G.L[2];
+        }
         d2 = a0 * a0 + a1 * a1 + a2 * a2;
         pid = q.id;
         if (A.rad) {
             // radical plane (section 2.1.1): |x|^2 - ri^2 <= |x - q|^2 - rj^2
-            const double ri = sh.gs.ri;
-            rj = A.rad[idx];
-            h = 0.5 * (d2 + radical_shift(ri, rj));
+            h = 0.5 * (d2 + radical_shift(sh.gs.ri, A.rad[idx]));
         } else {
             h = 0.5 * d2;
         }
-        bool self = (idx == sh.gs.si) && code == kNoShift;
-        // unique 32-bit keys: the high word of the distance (its exponent and
-        // 20 mantissa bits) with the low five bits replaced by the lane, so
-        // candidates closer than 2^-15 relative may swap; TEST ends a batch
-        // only past that resolution
-        if (!self && d2 < c.lim)
-            key = ((uint32_t)(__builtin_bit_cast(unsigned long long, d2) >> 32) & ~31u) | (uint32_t)gl;
+        valid = d2 < lim && !(idx == sh.gs.si && code == kNoShift);
     }
-    // the valid keys, compacted; each counts the smaller ones
-    const bool valid = key != ~0u;
-    const uint32_t gv = gbal<G>(valid, gb);
-    const int bn = __popc(gv);
-    if (valid) sh.u.w.x.key[__popc(gv & below)] = key;
+    unsigned long long vm = __builtin_amdgcn_ballot_w64(valid);
+    int width = 64;
+    if (__popcll(vm) > G) {
+        do {
+            width >>= 1;
+            vm &= (1ull << width) - 1;
+        } while (width > G && __popcll(vm) > G);
+        valid = valid && lane < width;
+    }
+    bn = __popcll(vm);
+    sh.gs.gc0 = c0 + width;
+    if (bn == 0) return PH_BATCH;
+    // unique 32-bit keys: the high word of the distance (its exponent and
+    // 20 mantissa bits) with the low five bits replaced by the place among
+    // the batch's particles, so candidates closer than 2^-15 relative may
+    // swap; TEST ends a batch only past that resolution
+    const int at = lane_rank(vm);
+    const uint32_t key = ((uint32_t)(__builtin_bit_cast(unsigned long long, d2) >> 32) & ~31u) | (uint32_t)at;
+    // each key counts the smaller ones, four at a time
+    if (valid) sh.u.w.x.key[at] = key;
+    if (lane < 3) sh.u.w.x.key[bn + lane] = ~0u;
     lds_fence();
     int rank = 0;
-    if (valid && bn > 1)
-        for (int j = 0; j < bn; j++) rank += sh.u.w.x.key[j] < key;
+    for (int j = 0; j < bn; j += 4) {
+        const uint4 k4 = *reinterpret_cast<const uint4 *>(&sh.u.w.x.key[j]);
+        rank += (k4.x < key) + (k4.y < key) + (k4.z < key) + (k4.w < key);
+    }
     if (valid) {
         // side-test bands with the radius bound of now: R only shrinks, so
         // a band taken now stays wide enough for every later test
-        const double R = radius_bound(c.rk);
+        const double R = radius_bound(rk);
         const double band = A.tau * ((fabs(a0) + fabs(a1) + fabs(a2)) * R + fabs(h));
         sh.u.w.cq[rank][0] = a0;
         sh.u.w.cq[rank][1] = a1;
@@ -548,12 +582,8 @@ __device__ __forceinline__ void ph_batch(const CellArgs &A, SL<G, S, MAXP, RAD> 
         sh.u.w.ccode[rank] = (uint8_t)code;
     }
     lds_fence();
-    sh.gs.gc0 += G;
-    c.bn = bn;
-    c.bk = 0;
-    // a candidate at distance zero (a coincident particle) sorts first
-    if (gbal<G>(valid && d2 == 0.0, gb)) c.phase = -ST_DUP;
-    else if (bn) c.phase = PH_TEST;
+    // a candidate at distance zero (a coincident particle)
+    return __builtin_amdgcn_ballot_w64(valid && d2 == 0.0) ? -ST_DUP : PH_TEST;
 }
 
 // ---- TEST: side of every vertex against the next candidates ----
@@ -1075,12 +1105,31 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G>
         }
         VC_PHASE_MARK(0, r_new);
         if (!__ballot(c.phase != PH_DONE)) break;
-        const bool r_gat = VC_PHASE_RAN(PH_GATHER);
-        if (c.phase == PH_GATHER) ph_gather<G, S, MAXP, F32, RAD>(A, sh, c, gl, gb, cnt);
-        VC_PHASE_MARK(1, r_gat);
-        const bool r_bat = VC_PHASE_RAN(PH_BATCH);
-        if (c.phase == PH_BATCH) ph_batch<G, S, MAXP, F32, RAD>(A, sh, c, gl, gb, below);
-        VC_PHASE_MARK(2, r_bat);
+        // each cell that needs particles searches until it has a batch to
+        // test or its search has ended
+        for (unsigned long long need = __builtin_amdgcn_ballot_w64(c.phase == PH_GATHER || c.phase == PH_BATCH); need;) {
+            const int l0 = __builtin_ctzll(need) & ~(G - 1);
+            need &= ~((unsigned long long)Gw<G>::FULL << l0);
+            SL<G, S, MAXP, RAD> &sg = shv[l0 / G];
+            const double lim = readlane_f64(c.lim, l0);
+            const uint32_t rk = (uint32_t)__builtin_amdgcn_readlane((int)c.rk, l0);
+            int ph = __builtin_amdgcn_readlane(c.phase, l0), bn = 0;
+            do {
+                if (ph == PH_GATHER) {
+                    ph = co_gather<G, S, MAXP, RAD>(A, sg, lane, lim);
+                    VC_PHASE_MARK(1, true);
+                }
+                if (ph == PH_BATCH) {
+                    ph = co_batch<G, S, MAXP, F32, RAD>(A, sg, lane, lim, rk, bn);
+                    VC_PHASE_MARK(2, true);
+                }
+            } while (ph == PH_GATHER || ph == PH_BATCH);
+            if (gb == l0) {
+                c.phase = ph;
+                c.bn = bn;
+                c.bk = 0;
+            }
+        }
 #ifdef VC_PHASE_CLOCKS
         const uint32_t t_cand = cnt[0];
 #endif
