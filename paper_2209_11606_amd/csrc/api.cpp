@@ -196,6 +196,7 @@ void set_bands(CellArgs &A, int force)
 {
     A.tau = (force & VC_FORCE_EXACT) ? 0x1p+600 : 0x1p-30;
     A.tau32 = (force & VC_FORCE_RECHECK) ? 0x1p+100f : 0x1p-21f;
+    A.kband32 = (double)A.tau32 / A.tau * 1.000001;
 }
 
 struct Launch {
@@ -383,7 +384,8 @@ vc_status create_common(vc_container *c, const double *xyz, const int64_t *offse
     c->launch.cpw = opts[0].cells_per_wave > 0 ? opts[0].cells_per_wave : 1;
     c->launch.vcap = opts[0].capacity;
     int cu = device_cu_count();
-    c->launch.waves = opts[0].waves > 0 ? opts[0].waves : cu * 16;
+    // twenty waves of the two-cell form are resident on a compute unit
+    c->launch.waves = opts[0].waves > 0 ? opts[0].waves : cu * (c->launch.cpw == 2 && dim == 3 ? 20 : 16);
     c->max_waves = std::max(c->launch.waves, cu * 32);
     c->htess.resize((size_t)ntess);
     int64_t nb = 0;
@@ -597,7 +599,7 @@ vc_status tune(vc_container *b, vc_result *r, hipStream_t s, const int32_t *list
     const int cu = device_cu_count();
     const int form_c[][3] = {{1, 2, 128}, {1, 4, 256}, {2, 2, 64}, {4, 4, 64}};  // cpw, slots, capacity
     const int chunk_c[] = {1, 4, 16, 64};
-    const int waves_c[] = {cu * 8, cu * 16, cu * 32};
+    const int waves_c[] = {cu * 8, cu * 16, cu * 20};
     Launch best_of_form[4];
     float ms_of_form[4];
     for (int fi = 0; fi < 4; fi++) {

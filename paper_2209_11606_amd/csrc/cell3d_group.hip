@@ -25,10 +25,10 @@
 // GATHER reads the particle counts of up to 64 blocks and BATCH loads up to
 // 64 particles, keeps those inside the radius bound and sorts them by distance
 // (a rank count over the keys), both with the whole wave for one cell at a
-// time.  TEST takes the sorted candidates one at a time, and a conflict parks the group in CUT.  The cut itself (the
-// costliest step) runs only once no group of the wave can advance without
-// one, so that the cuts of the wave's cells run in the same instructions
-// instead of one after another.  STATS (volume, centroid, counts, face
+// time.  TEST takes the sorted candidates one at a time, and a conflict
+// parks the group in CUT.  The cut itself (the costliest step) runs only once
+// no group of the wave can advance without one, so that the cuts of the
+// wave's cells run in the same instructions instead of one after another.  STATS (volume, centroid, counts, face
 // orders, neighbours) is deferred in the same way.
 //
 // All masks are the group's bit fields (32 bits), reductions are DPP row
@@ -47,14 +47,26 @@ struct Gw {
     static constexpr uint32_t FULL = G >= 32 ? 0xffffffffu : ((1u << G) - 1u);
 };
 
-constexpr int kFirstBlocks = 16;  // blocks of a cell's first gather
+// blocks of a cell's first gather (periodic 10^6, two cells per wave, step: 8
+// blocks 10.05 ms, 12 9.84, 16 9.80, 24 9.73, 32 9.77)
+constexpr int kFirstBlocks = 24;
 
+// a negative phase is a failure (-ST_*)
 enum { PH_NEW, PH_GATHER, PH_BATCH, PH_TEST, PH_CUT, PH_STATS, PH_DONE };
 
 __device__ __forceinline__ void lds_fence()
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     __builtin_amdgcn_wave_barrier();
+}
+
+// A value the compiler cannot see through: what is computed from it stays
+// where it is used.  Without it lane constants (addresses, masks, slot
+// numbers) are kept in registers over the whole search loop, and others spill.
+__device__ __forceinline__ int opaque(int v)
+{
+    __asm__ volatile("" : "+v"(v));
+    return v;
 }
 
 // the group's bits of a wave ballot
@@ -166,8 +178,18 @@ struct GState {
     int cur;                // next offset index
     int gtot, gc0;          // candidates of the gather, next batch start
     int cell, cend;         // claimed range of the work queue
-    int tcur;               // the tessellation whose record is in the group's Tess
+    int tess;               // its tessellation
     uint32_t cnt[DC_N];     // counters other than candidates and tests
+};
+
+// A candidate of the batch.  dk orders it: the high word of |q|^2 less 2^-15
+// of it (the batch's sorting resolution), with the image code in the low seven
+// bits.
+struct alignas(16) Cand {
+    double q[3], h;  // the plane q.r = h
+    double band;     // FP64 side-test band
+    int32_t id;      // particle
+    uint32_t dk;
 };
 
 // The group's LDS.  The radical instantiation has the same layout: its
@@ -177,7 +199,6 @@ template <int G, int S, int MAXP, bool RAD>
 struct SL {
     alignas(16) double pq[MAXP][4];  // planes n.r = h (n = q for a bisector, h = |q|^2 / 2)
     GState gs;
-    Tess T;                 // the cell's tessellation
     int32_t plab[MAXP];
     uint8_t psh[MAXP];
     // edge k of slot t is number 4 t + k: nb[it] is the number of the same
@@ -185,20 +206,21 @@ struct SL {
     alignas(4) uint8_t nb[4 * G * S];
     union alignas(16) {
         struct {               // the search
-            double cq[G][6];   // the batch's candidates, nearest first: q, plane offset h,
-                               // |q|^2 (1 - 2^-14), FP64 side-test band
-            union {
-                alignas(16) uint32_t key[G + 4];  // ranking keys (BATCH only)
-                float cfb[G];                     // then: the FP32 side-test bands (FP32 filter)
-            } x;
-            int32_t cid[G];
+            Cand cq[G];        // the batch's candidates, nearest first
             int32_t cpre[65];  // the gather's blocks: particles before, first particle less that,
-            int32_t coff[64];  // image code | shifts + 2 in 3-bit fields << 7
-            uint16_t csh[64];
-            uint8_t mark[64];  // BATCH: block of each lane
-            uint8_t ccode[G];
-            uint32_t bedge[G * S];  // CUT: boundary edges a | b << 8 | number << 16
-            uint8_t first[MAXP];    // CUT: 4 x slot of the new triangle whose first plane is a
+            int32_t coff[64];  // image code
+            uint8_t ccode[64];
+            union {
+                double off[6];                        // NEW: corner offsets
+                struct {                              // BATCH: ranking keys, block of each lane
+                    alignas(16) uint32_t key[G + 4];
+                    uint8_t mark[64];
+                } b;
+                struct {                              // CUT: boundary edges a | b << 8 | number << 16,
+                    uint32_t bedge[G * S];            // 4 x slot of the new triangle whose first plane is a
+                    uint8_t first[MAXP];
+                } c;
+            } x;
         } w;
         struct {               // the statistics of the finished cell
             double pos[G * S][3];
@@ -224,6 +246,7 @@ struct SCell {
     uint32_t hw[S];              // squared vertex norm: its high word plus one; 0 for a free slot
     uint32_t rk;                 // their maximum over the cell
     double lim;                  // squared search radius (upper bound)
+    uint32_t dlim;               // its high word, the low seven bits set: a candidate whose dk is above lies beyond
     int phase;
     int bn, bk;                  // candidates of the batch, next one
 };
@@ -263,6 +286,7 @@ __device__ __forceinline__ void update_radius(SCell<S, F32> &c, const CellArgs &
     c.rk = m;
     const double R2 = __builtin_bit_cast(double, (unsigned long long)m << 32);
     c.lim = A.rad ? search_lim(R2, radius_bound(m), A, ri) : 4.0 * R2 * kMargin;
+    c.dlim = (uint32_t)(__builtin_bit_cast(unsigned long long, c.lim) >> 32) | 127u;
 }
 
 template <int G, int S, int MAXP, bool F32, bool RAD>
@@ -290,103 +314,6 @@ __device__ __forceinline__ void cell_fail(const CellArgs &A, SL<G, S, MAXP, RAD>
     c.phase = PH_NEW;
 }
 
-// ---- NEW: claim the next cell and set up the box (Eq. 1-2) ----
-template <int G, int S, int MAXP, bool F32, bool RAD>
-__device__ __forceinline__ void ph_new(const CellArgs &A, SL<G, S, MAXP, RAD> &sh, SCell<S, F32> &c, int ncell, int gl,
-                                       int gb)
-{
-    if (sh.gs.cell >= sh.gs.cend) {
-        int base = 0;
-        if (gl == 0) base = atomicAdd(A.queue, A.chunk);
-        base = __shfl(base, gb);
-        sh.gs.cell = base;
-        sh.gs.cend = min(base + A.chunk, ncell);
-    }
-    if (sh.gs.cell >= sh.gs.cend) {
-        c.phase = PH_DONE;
-        return;
-    }
-    const int si = A.cell_list ? A.cell_list[sh.gs.cell] : sh.gs.cell;
-    sh.gs.cell++;
-    const Particle me = A.part[si];
-    sh.gs.si = si;
-    sh.gs.id = me.id;
-    sh.gs.ri = A.rad ? A.rad[si] : 0.0;
-    sh.gs.p[0] = me.x;
-    sh.gs.p[1] = me.y;
-    sh.gs.p[2] = me.z;
-    if (me.tess != sh.gs.tcur) {
-        // cells come in block order, so the record changes once per
-        // tessellation of a batch
-        const int32_t *src = (const int32_t *)&A.tess[me.tess];
-        int32_t *dst = (int32_t *)&sh.T;
-        for (int k = gl; k < (int)(sizeof(Tess) / 4); k += G) dst[k] = src[k];
-        lds_fence();
-        sh.gs.tcur = me.tess;
-    }
-    lds_fence();
-    const Grid &G3 = sh.T.G;
-#pragma unroll
-    for (int d = 0; d < 3; d++) {
-        const int k = block_coord(G3, sh.gs.p[d], d);
-        sh.gs.bc[d] = k;
-        sh.gs.fl[d] = offset_flip(G3, sh.gs.p[d], k, d);
-    }
-    if (gl < 6) {
-        // face 2d + side of the box (Eq. 1-2, clipped as in section 3.1.3)
-        const int d = gl >> 1, side = gl & 1;
-        const double pd = d == 0 ? sh.gs.p[0] : (d == 1 ? sh.gs.p[1] : sh.gs.p[2]);
-        const BoxSide b = box_side(sh.T, pd, d, side, sh.gs.id);
-        sh.plab[gl] = b.lab;
-        sh.psh[gl] = b.code;
-        sh.pq[gl][0] = d == 0 ? b.nd : 0.0;
-        sh.pq[gl][1] = d == 1 ? b.nd : 0.0;
-        sh.pq[gl][2] = d == 2 ? b.nd : 0.0;
-        sh.pq[gl][3] = b.h;
-    }
-#pragma unroll
-    for (int s = 0; s < S; s++) {
-        c.tp[s] = 0;
-        c.vx[s] = c.vy[s] = c.vz[s] = 0.0;
-        c.fx[s] = c.fy[s] = c.fz[s] = 0.0f;
-        c.live[s] = 0;
-        c.conf[s] = 0;
-        c.hw[s] = 0;
-    }
-    c.live[0] = 0xffu;
-    if (gl < 8) {
-        int bx = gl & 1, by = (gl >> 1) & 1, bz = (gl >> 2) & 1;
-        int X = bx, Y = 2 + by, Z = 4 + bz;
-        int neg = 3 - bx - by - bz;
-        c.tp[0] = (neg & 1) ? (X | (Z << 8) | (Y << 16)) : (X | (Y << 8) | (Z << 16));
-        double e[3];
-#pragma unroll
-        for (int d = 0; d < 3; d++) {
-            const int b = (gl >> d) & 1;
-            const double o = box_side(sh.T, sh.gs.p[d], d, b, sh.gs.id).off;
-            e[d] = b ? o : -o;
-        }
-        c.vx[0] = e[0];
-        c.vy[0] = e[1];
-        c.vz[0] = e[2];
-        c.fx[0] = (float)e[0];
-        c.fy[0] = (float)e[1];
-        c.fz[0] = (float)e[2];
-        c.hw[0] = norm_key(e[0], e[1], e[2]);
-        // the corners across the edges of planes X Y, Y Z and Z X differ in z,
-        // x and y; a corner and its neighbour list these planes in opposite
-        // senses, so a corner's edges 0, 1, 2 are its neighbours' 2, 1, 0
-        const int nz = 4 * (gl ^ 4), nx = 4 * (gl ^ 1), ny = 4 * (gl ^ 2);
-        reinterpret_cast<uint32_t *>(sh.nb)[gl] =
-            (uint32_t)(((neg & 1) ? ny : nz) + 2) | (uint32_t)(nx + 1) << 8 | (uint32_t)((neg & 1) ? nz : ny) << 16;
-    }
-    c.used = 0x3fu;
-    lds_fence();
-    update_radius<G, S, F32>(c, A, sh.gs.ri);
-    sh.gs.cur = 0;
-    c.phase = PH_GATHER;
-}
-
 // The search steps take all 64 lanes for one cell: a wave's cells seldom
 // need particles at the same moment, and a step for one cell costs the wave
 // the same with 64 lanes as with G.  The cell's values are wave-uniform here
@@ -409,6 +336,111 @@ __device__ __forceinline__ int wave_max_scan(int v)
 
 typedef const __attribute__((address_space(4))) Tess *TessConst;
 typedef const __attribute__((address_space(4))) Offset *OffsetConst;
+typedef const __attribute__((address_space(4))) Particle *ParticleConst;
+
+// ---- NEW: claim the next cell and set up the box (Eq. 1-2) ----
+// Returns the next phase; `in`: the lanes of the cell's group.
+template <int G, int S, int MAXP, bool F32, bool RAD>
+__device__ __forceinline__ int co_new(const CellArgs &A, SL<G, S, MAXP, RAD> &sh, SCell<S, F32> &c, int ncell, int lane,
+                                      bool in)
+{
+    int cell = __builtin_amdgcn_readfirstlane(sh.gs.cell), cend = __builtin_amdgcn_readfirstlane(sh.gs.cend);
+    if (cell >= cend) {
+        int base = 0;
+        if (lane == 0) base = atomicAdd(A.queue, A.chunk);
+        cell = __builtin_amdgcn_readfirstlane(base);
+        cend = min(cell + A.chunk, ncell);
+        if (cell >= cend) return PH_DONE;
+        sh.gs.cend = cend;
+    }
+    sh.gs.cell = cell + 1;
+    const int si = A.cell_list ? __builtin_amdgcn_readfirstlane(A.cell_list[cell]) : cell;
+    ParticleConst me = (ParticleConst)(uintptr_t)(A.part + si);
+    const double p[3] = {me->x, me->y, me->z};
+    const int id = me->id, tess = me->tess;
+    const double ri = A.rad ? A.rad[si] : 0.0;
+    TessConst T = (TessConst)(uintptr_t)(A.tess + tess);
+    sh.gs.si = si;
+    sh.gs.id = id;
+    sh.gs.ri = ri;
+    sh.gs.tess = tess;
+    sh.gs.cur = 0;
+#pragma unroll
+    for (int d = 0; d < 3; d++) {
+        // as block_coord and offset_flip
+        const int g = T->G.g[d];
+        const double lo = T->G.lo[d], bs = T->G.bs[d];
+        const int k = min(max((int)floor((p[d] - lo) * T->G.inv_bs[d]), 0), g - 1);
+        sh.gs.p[d] = p[d];
+        sh.gs.bc[d] = k;
+        sh.gs.fl[d] = (p[d] - (lo + k * bs)) * 2.0 > bs ? -1 : 1;
+    }
+    if (lane < 6) {
+        // face 2d + side of the box (Eq. 1-2, clipped as in section 3.1.3),
+        // as box_side
+        const int d = lane >> 1, side = lane & 1;
+        const bool d0 = d == 0, d1 = d == 1;
+        const double pd = d0 ? p[0] : (d1 ? p[1] : p[2]), L = d0 ? T->G.L[0] : (d1 ? T->G.L[1] : T->G.L[2]);
+        const double lo = d0 ? T->G.lo[0] : (d1 ? T->G.lo[1] : T->G.lo[2]);
+        const double hi = d0 ? T->G.hi[0] : (d1 ? T->G.hi[1] : T->G.hi[2]);
+        const bool per = (d0 ? T->G.per[0] : (d1 ? T->G.per[1] : T->G.per[2])) != 0;
+        const double sg = side ? 1.0 : -1.0;
+        double off = per ? 0.5 * L : (side ? hi - pd : -(lo - pd));
+        double nd = per ? sg * L : sg, h = per ? 0.5 * (L * L) : off;
+        int lab = per ? id : -(2 * d + side + 1), code = kNoShift;
+        if (per) code += (side ? 1 : -1) * (d0 ? 1 : (d1 ? 5 : 25));
+        const double clip = T->clip_half;
+        if (clip > 0.0 && clip < off) {
+            nd = sg;
+            h = off = clip;
+            lab = -(7 + 2 * d + side);
+            code = kNoShift;
+        }
+        sh.plab[lane] = lab;
+        sh.psh[lane] = (uint8_t)code;
+        sh.pq[lane][0] = d0 ? nd : 0.0;
+        sh.pq[lane][1] = d1 ? nd : 0.0;
+        sh.pq[lane][2] = d == 2 ? nd : 0.0;
+        sh.pq[lane][3] = h;
+        sh.u.w.x.off[lane] = side ? off : -off;
+    }
+    lds_fence();
+    if (in) {
+        const int gl = lane % G;
+#pragma unroll
+        for (int s = 0; s < S; s++) {
+            c.tp[s] = 0;
+            c.vx[s] = c.vy[s] = c.vz[s] = 0.0;
+            c.fx[s] = c.fy[s] = c.fz[s] = 0.0f;
+            c.live[s] = 0;
+            c.conf[s] = 0;
+            c.hw[s] = 0;
+        }
+        c.live[0] = 0xffu;
+        if (gl < 8) {
+            const int bx = gl & 1, by = (gl >> 1) & 1, bz = (gl >> 2) & 1;
+            const int X = bx, Y = 2 + by, Z = 4 + bz, neg = 3 - bx - by - bz;
+            c.tp[0] = (neg & 1) ? (X | (Z << 8) | (Y << 16)) : (X | (Y << 8) | (Z << 16));
+            c.vx[0] = sh.u.w.x.off[X];
+            c.vy[0] = sh.u.w.x.off[Y];
+            c.vz[0] = sh.u.w.x.off[Z];
+            c.fx[0] = (float)c.vx[0];
+            c.fy[0] = (float)c.vy[0];
+            c.fz[0] = (float)c.vz[0];
+            c.hw[0] = norm_key(c.vx[0], c.vy[0], c.vz[0]);
+            // the corners across the edges of planes X Y, Y Z and Z X differ in z,
+            // x and y; a corner and its neighbour list these planes in opposite
+            // senses, so a corner's edges 0, 1, 2 are its neighbours' 2, 1, 0
+            const int nz = 4 * (gl ^ 4), nx = 4 * (gl ^ 1), ny = 4 * (gl ^ 2);
+            reinterpret_cast<uint32_t *>(sh.nb)[gl] =
+                (uint32_t)(((neg & 1) ? ny : nz) + 2) | (uint32_t)(nx + 1) << 8 | (uint32_t)((neg & 1) ? nz : ny) << 16;
+        }
+        c.used = 0x3fu;
+        update_radius<G, S, F32>(c, A, ri);
+    }
+    lds_fence();
+    return PH_GATHER;
+}
 
 // ---- GATHER: particle counts of the next blocks of the offset list ----
 // The first gather takes kFirstBlocks blocks, whose cuts bring the search
@@ -417,7 +449,7 @@ typedef const __attribute__((address_space(4))) Offset *OffsetConst;
 template <int G, int S, int MAXP, bool RAD>
 __device__ __forceinline__ int co_gather(const CellArgs &A, SL<G, S, MAXP, RAD> &sh, int lane, double lim)
 {
-    TessConst T = (TessConst)(uintptr_t)(A.tess + __builtin_amdgcn_readfirstlane(sh.gs.tcur));
+    TessConst T = (TessConst)(uintptr_t)(A.tess + __builtin_amdgcn_readfirstlane(sh.gs.tess));
     const int cur = __builtin_amdgcn_readfirstlane(sh.gs.cur);
     // past the offset list: the shell search of the block bound is the
     // one-cell kernel's (the spill pass), as for the extended cells below
@@ -430,7 +462,7 @@ __device__ __forceinline__ int co_gather(const CellArgs &A, SL<G, S, MAXP, RAD> 
     // blocks against the balls and takes 64 blocks of a shell per step
     const bool far = lim > 16.0 * T->bsmin2;
     if (cur >= G && far) return -ST_CAP;
-    const int width = cur == 0 ? kFirstBlocks : (far ? G - cur : 64);
+    const int width = cur == 0 ? min(kFirstBlocks, G) : (far ? G - cur : 64);
     const int o = cur + lane;
     bool ok = lane < width && o < A.noff;
     const Offset of = ok ? A.offs[o] : Offset{0, 0, 0, 0};
@@ -481,8 +513,7 @@ __device__ __forceinline__ int co_gather(const CellArgs &A, SL<G, S, MAXP, RAD> 
     sh.u.w.cpre[lane] = incl - cntb;
     sh.u.w.cpre[64] = total;
     sh.u.w.coff[lane] = beg - (incl - cntb);
-    sh.u.w.csh[lane] = (uint16_t)((25 * (sv[2] + 2) + 5 * (sv[1] + 2) + (sv[0] + 2)) |
-                                  (((sv[0] + 2) | ((sv[1] + 2) << 3) | ((sv[2] + 2) << 6)) << 7));
+    sh.u.w.ccode[lane] = (uint8_t)(25 * (sv[2] + 2) + 5 * (sv[1] + 2) + (sv[0] + 2));
     sh.gs.gtot = total;
     sh.gs.gc0 = 0;
     lds_fence();
@@ -502,28 +533,28 @@ __device__ __forceinline__ int co_batch(const CellArgs &A, SL<G, S, MAXP, RAD> &
     // the block of each particle: blocks mark the lane of their first one,
     // and a lane's block is the last mark at or below it
     const int pre = sh.u.w.cpre[lane], nxt = sh.u.w.cpre[lane + 1];
-    sh.u.w.mark[lane] = 0;
+    sh.u.w.x.b.mark[lane] = 0;
     lds_fence();
-    if (nxt > pre && nxt > c0 && pre < c0 + 64) sh.u.w.mark[max(pre - c0, 0)] = (uint8_t)(lane + 1);
+    if (nxt > pre && nxt > c0 && pre < c0 + 64) sh.u.w.x.b.mark[max(pre - c0, 0)] = (uint8_t)(lane + 1);
     lds_fence();
-    const int b = max(wave_max_scan(sh.u.w.mark[lane]) - 1, 0);
+    const int b = max(wave_max_scan(sh.u.w.x.b.mark[lane]) - 1, 0);
     const int ci = c0 + lane;
     bool valid = ci < tot;
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, d2 = 0.0, h = 0.0;
     int pid = 0, code = 0;
     if (valid) {
         const int idx = sh.u.w.coff[b] + ci;
-        const int cs = sh.u.w.csh[b];
-        code = cs & 0x7f;
+        code = sh.u.w.ccode[b];
         const Particle q = A.part[idx];
         a0 = q.x - sh.gs.p[0];
         a1 = q.y - sh.gs.p[1];
         a2 = q.z - sh.gs.p[2];
         if (code != kNoShift) {
-            const int s0 = ((cs >> 7) & 7) - 2, s1 = ((cs >> 10) & 7) - 2, s2 = ((cs >> 13) & 7) - 2;
-            if (s0) a0 = a0 + s0 * sh.T.G.L[0];
-            if (s1) a1 = a1 + s1 * sh.T.G.L[1];
-            if (s2) a2 = a2 + s2 * sh.T.G.L[2];
+            TessConst T = (TessConst)(uintptr_t)(A.tess + __builtin_amdgcn_readfirstlane(sh.gs.tess));
+            const int s0 = code % 5 - 2, s1 = code / 5 % 5 - 2, s2 = code / 25 - 2;
+            if (s0) a0 = a0 + s0 * T->G.L[0];
+            if (s1) a1 = a1 + s1 * T->G.L[1];
+            if (s2) a2 = a2 + s2 * T->G.L[2];
         }
         d2 = a0 * a0 + a1 * a1 + a2 * a2;
         pid = q.id;
@@ -554,12 +585,12 @@ __device__ __forceinline__ int co_batch(const CellArgs &A, SL<G, S, MAXP, RAD> &
     const int at = lane_rank(vm);
     const uint32_t key = ((uint32_t)(__builtin_bit_cast(unsigned long long, d2) >> 32) & ~31u) | (uint32_t)at;
     // each key counts the smaller ones, four at a time
-    if (valid) sh.u.w.x.key[at] = key;
-    if (lane < 3) sh.u.w.x.key[bn + lane] = ~0u;
+    if (valid) sh.u.w.x.b.key[at] = key;
+    if (lane < 3) sh.u.w.x.b.key[bn + lane] = ~0u;
     lds_fence();
     int rank = 0;
     for (int j = 0; j < bn; j += 4) {
-        const uint4 k4 = *reinterpret_cast<const uint4 *>(&sh.u.w.x.key[j]);
+        const uint4 k4 = *reinterpret_cast<const uint4 *>(&sh.u.w.x.b.key[j]);
         rank += (k4.x < key) + (k4.y < key) + (k4.z < key) + (k4.w < key);
     }
     if (valid) {
@@ -567,19 +598,8 @@ __device__ __forceinline__ int co_batch(const CellArgs &A, SL<G, S, MAXP, RAD> &
         // a band taken now stays wide enough for every later test
         const double R = radius_bound(rk);
         const double band = A.tau * ((fabs(a0) + fabs(a1) + fabs(a2)) * R + fabs(h));
-        sh.u.w.cq[rank][0] = a0;
-        sh.u.w.cq[rank][1] = a1;
-        sh.u.w.cq[rank][2] = a2;
-        sh.u.w.cq[rank][3] = h;
-        sh.u.w.cq[rank][4] = d2 * (1.0 - 0x1p-14);
-        sh.u.w.cq[rank][5] = band;
-        if (F32) {
-            const float g0 = (float)a0, g1 = (float)a1, g2 = (float)a2, gh = (float)h;
-            sh.u.w.x.cfb[rank] =
-                A.tau32 * ((fabsf(g0) + fabsf(g1) + fabsf(g2)) * ((float)R * 1.0000001f) + fabsf(gh));
-        }
-        sh.u.w.cid[rank] = pid;
-        sh.u.w.ccode[rank] = (uint8_t)code;
+        const uint32_t hd = max((uint32_t)(__builtin_bit_cast(unsigned long long, d2) >> 32), 32u) - 32u;
+        sh.u.w.cq[rank] = Cand{{a0, a1, a2}, h, band, pid, (hd & ~127u) | (uint32_t)code};
     }
     lds_fence();
     // a candidate at distance zero (a coincident particle)
@@ -610,16 +630,17 @@ __device__ __forceinline__ void ph_test(const CellArgs &A, SL<G, S, MAXP, RAD> &
     int hit = 0;  // 1: conflict, 2: in-band vertex
     for (;;) {
         if (k >= c.bn) break;
-        const double q0 = sh.u.w.cq[k][0], q1 = sh.u.w.cq[k][1], q2 = sh.u.w.cq[k][2], h = sh.u.w.cq[k][3];
-        const double d2 = sh.u.w.cq[k][4], band = sh.u.w.cq[k][5];
+        const Cand &cd = sh.u.w.cq[k];
+        const double q0 = cd.q[0], q1 = cd.q[1], q2 = cd.q[2], h = cd.h, band = cd.band;
+        // past this bound the rest of the batch is beyond the search radius
+        // too (a candidate just beyond it is tested and cuts nothing)
+        const bool beyond = cd.dk > c.dlim;
         // issue the candidate's three LDS reads together, ahead of the range test
         __asm__ volatile("" ::: "memory");
-        // sorted to within 2^-15: past this bound the rest of the batch is
-        // beyond the radius bound too (a candidate just beyond it is tested
-        // and cuts nothing)
-        if (d2 >= c.lim) break;
+        if (beyond) break;
         if (F32) {
-            const float g0 = (float)q0, g1 = (float)q1, g2 = (float)q2, gh = (float)h, band32 = sh.u.w.x.cfb[k];
+            const float g0 = (float)q0, g1 = (float)q1, g2 = (float)q2, gh = (float)h;
+            const float band32 = (float)(band * A.kband32);
             unsigned long long wu[S], wun = 0;
 #pragma unroll
             for (int s = 0; s < S; s++) {
@@ -711,6 +732,25 @@ __device__ __forceinline__ void ph_test(const CellArgs &A, SL<G, S, MAXP, RAD> &
     }
 }
 
+// vertex of planes A, B, C by Cramer's rule, with the reciprocal of the
+// determinant by two Newton steps (to an ulp, like a division, where the
+// determinant is a normal number with a normal reciprocal; elsewhere the
+// vertex is not finite and the cell goes to the one-cell kernel)
+__device__ __forceinline__ void cut_vertex(const double *A, const double *B, const double *C, double &x, double &y,
+                                           double &z)
+{
+    const double bc0 = B[1] * C[2] - B[2] * C[1], bc1 = B[2] * C[0] - B[0] * C[2], bc2 = B[0] * C[1] - B[1] * C[0];
+    const double ca0 = C[1] * A[2] - C[2] * A[1], ca1 = C[2] * A[0] - C[0] * A[2], ca2 = C[0] * A[1] - C[1] * A[0];
+    const double ab0 = A[1] * B[2] - A[2] * B[1], ab1 = A[2] * B[0] - A[0] * B[2], ab2 = A[0] * B[1] - A[1] * B[0];
+    const double det = A[0] * bc0 + A[1] * bc1 + A[2] * bc2;
+    double inv = __builtin_amdgcn_rcp(det);
+    inv = fma(inv, fma(-det, inv, 1.0), inv);
+    inv = fma(inv, fma(-det, inv, 1.0), inv);
+    x = (A[3] * bc0 + B[3] * ca0 + C[3] * ab0) * inv;
+    y = (A[3] * bc1 + B[3] * ca1 + C[3] * ab1) * inv;
+    z = (A[3] * bc2 + B[3] * ca2 + C[3] * ab2) * inv;
+}
+
 // ---- CUT: remove the conflict region, fan new triangles around the plane ----
 // The kernel is bound by instruction issue and the cut is its costliest step,
 // so the triangles across a slot's edges are kept by edge number (nb): a
@@ -727,10 +767,11 @@ __device__ __forceinline__ void ph_cut(const CellArgs &A, SL<G, S, MAXP, RAD> &s
     const int k = c.bk;
     int p = free_plane<MAXP>(c.used);
     if (p < 0) {
+        // the planes of the kept vertices (one that loses all of them is free)
         uint32_t u = 0;
 #pragma unroll
         for (int s = 0; s < S; s++)
-            if ((c.live[s] >> gl) & 1)
+            if (((c.live[s] & ~c.conf[s]) >> gl) & 1)
 #pragma unroll
                 for (int j = 0; j < 3; j++) u |= 1u << ((c.tp[s] >> (8 * j)) & 0xff);
         // group OR of the plane masks
@@ -746,23 +787,22 @@ __device__ __forceinline__ void ph_cut(const CellArgs &A, SL<G, S, MAXP, RAD> &s
     // boundary edges of the conflict region (conflict triangle edges whose
     // twin triangle is kept), listed edge by edge of each slot
     const uint32_t *nbw = reinterpret_cast<const uint32_t *>(sh.nb);
-    unsigned long long cf = 0;
+    unsigned long long keep = 0;
 #pragma unroll
-    for (int s = 0; s < S; s++) cf |= (unsigned long long)c.conf[s] << (s * G);
+    for (int s = 0; s < S; s++) keep |= (unsigned long long)(~c.conf[s] & Gw<G>::FULL) << (s * G);
     int m = 0;
 #pragma unroll
     for (int s = 0; s < S; s++) {
         if (s > 0 && !__builtin_amdgcn_ballot_w64(c.conf[s] != 0)) continue;
-        const bool mine = (c.conf[s] >> gl) & 1;
-        const uint32_t w = nbw[s * G + gl], t3 = c.tp[s];
+        const uint32_t w = nbw[s * G + gl], t3 = c.tp[s], mine = (c.conf[s] >> gl) & 1;
 #pragma unroll
         for (int j = 0; j < 3; j++) {
-            const bool bd = mine && !((cf >> ((w >> (8 * j + 2)) & (G * S - 1))) & 1);
-            const uint32_t mb = gbal<G>(bd, gb);
+            const uint32_t bd = (uint32_t)(keep >> ((w >> (8 * j + 2)) & (G * S - 1))) & mine;
+            const uint32_t mb = gbal<G>(bd != 0, gb);
             const int o = m + __popc(mb & below);
             // bytes: planes a, b of the edge, its number in the kept triangle
-            if (bd && o < G * S)
-                sh.u.w.bedge[o] = __builtin_amdgcn_perm(w, t3, 0x0c000000 | (4 + j) << 16 | ((j + 1) % 3) << 8 | j);
+            if (bd != 0 && o < G * S)
+                sh.u.w.x.c.bedge[o] = __builtin_amdgcn_perm(w, t3, 0x0c000000 | (4 + j) << 16 | ((j + 1) % 3) << 8 | j);
             m += __popc(mb);
         }
     }
@@ -777,14 +817,15 @@ __device__ __forceinline__ void ph_cut(const CellArgs &A, SL<G, S, MAXP, RAD> &s
         c.phase = -ST_CAP;
         return;
     }
-    const double *C = sh.u.w.cq[k];
+    const Cand &cd = sh.u.w.cq[k];
+    const double C[4] = {cd.q[0], cd.q[1], cd.q[2], cd.h};
     if (gl == 0) {
         sh.pq[p][0] = C[0];
         sh.pq[p][1] = C[1];
         sh.pq[p][2] = C[2];
         sh.pq[p][3] = C[3];
-        sh.plab[p] = sh.u.w.cid[k];
-        sh.psh[p] = sh.u.w.ccode[k];
+        sh.plab[p] = cd.id;
+        sh.psh[p] = (uint8_t)(cd.dk & 127u);
     }
     lds_fence();
     // free slots in slot order take the new triangles (a, b, p) by rank; the
@@ -795,8 +836,10 @@ __device__ __forceinline__ void ph_cut(const CellArgs &A, SL<G, S, MAXP, RAD> &s
 #pragma unroll
     for (int s = 0; s < S; s++) {
         const int rk = before + __popc(fr[s] & below);
-        take[s] = ((fr[s] >> gl) & 1) && rk < m;
+        // one compare: a slot that is not free ranks past every triangle
+        take[s] = rk + (int)((~fr[s] >> gl & 1) << 16) < m;
         before += __popc(fr[s]);
+        const uint32_t tk = gbal<G>(take[s], gb);
         if ((c.conf[s] >> gl) & 1) {
             // a freed slot holds the particle (TEST) until it is taken
             c.vx[s] = c.vy[s] = c.vz[s] = 0.0;
@@ -804,10 +847,10 @@ __device__ __forceinline__ void ph_cut(const CellArgs &A, SL<G, S, MAXP, RAD> &s
             c.hw[s] = 0;
         }
         if (take[s]) {
-            ed[s] = sh.u.w.bedge[rk];
+            ed[s] = sh.u.w.x.c.bedge[rk];
             const int a = ed[s] & 0xff, b = (ed[s] >> 8) & 0xff;
             double x, y, z;
-            cramer(sh.pq[a], sh.pq[b], C, x, y, z);
+            cut_vertex(sh.pq[a], sh.pq[b], C, x, y, z);
             c.tp[s] = (ed[s] & 0xffff) | ((uint32_t)p << 16);
             c.vx[s] = x;
             c.vy[s] = y;
@@ -818,9 +861,9 @@ __device__ __forceinline__ void ph_cut(const CellArgs &A, SL<G, S, MAXP, RAD> &s
                 c.fz[s] = (float)z;
             }
             c.hw[s] = norm_key(x, y, z);
-            sh.u.w.first[a] = (uint8_t)(4 * (s * G + gl));
+            sh.u.w.x.c.first[a] = (uint8_t)(4 * (s * G + gl));
         }
-        c.live[s] = (c.live[s] & ~c.conf[s]) | gbal<G>(take[s], gb);
+        c.live[s] = (c.live[s] & ~c.conf[s]) | tk;
         c.conf[s] = 0;
     }
     lds_fence();
@@ -829,7 +872,7 @@ __device__ __forceinline__ void ph_cut(const CellArgs &A, SL<G, S, MAXP, RAD> &s
 #pragma unroll
     for (int s = 0; s < S; s++) {
         if (take[s]) {
-            const int t = 4 * (s * G + gl), e = ed[s] >> 16, nx = (sh.u.w.first[(ed[s] >> 8) & 0xff] & 0xfc) | 2;
+            const int t = 4 * (s * G + gl), e = ed[s] >> 16, nx = (sh.u.w.x.c.first[(ed[s] >> 8) & 0xff] & 0xfc) | 2;
             *reinterpret_cast<uint16_t *>(sh.nb + t) = (uint16_t)(e | nx << 8);
             sh.nb[nx] = (uint8_t)(t + 1);
             sh.nb[e] = (uint8_t)t;
@@ -1038,19 +1081,20 @@ __device__ __forceinline__ void flush_counters(const CellArgs &A, SL<G, S, MAXP,
 }
 
 // Occupancy target in waves per SIMD, to which the register allocator is
-// held.  The two-cells-per-wave form runs four waves: 128 registers and,
-// with 32 plane slots per cell, 10,016 bytes of LDS per wave (of the 10,240
-// that sixteen waves per compute unit leave); a cell that needs more plane
-// slots goes to the spill pass.  (The instantiation that writes Weinberg
-// records spills more registers at that budget, around the record's call,
-// and is still faster than at three waves.)
-template <int G>
+// held.  The two-cells-per-wave form runs five waves: 96 registers, with 18
+// spilled, and 8,032 bytes of LDS per wave (of the 8,192 that twenty waves per
+// compute unit leave); a cell that needs more than 32 plane slots goes to the
+// spill pass.  At four waves nothing is spilled and the periodic 10^6 step
+// takes 9.25 ms against 8.69.  The instantiation that writes Weinberg records
+// spills 61 registers at 96, around the record's call, and stays at four (VoroTop
+// 200,000: 4.81 ms a step against 5.00).
+template <int G, bool WB>
 struct SyncWaves {
-    static constexpr int value = G == 32 ? 4 : 2;
+    static constexpr int value = G == 32 ? (WB ? 4 : 5) : 2;
 };
 
 template <int G, int S, int MAXP, bool F32, bool RAD, bool WB>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G>::value))) void k_cells_sync(CellArgs Ain)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G, WB>::value))) void k_cells_sync(CellArgs Ain)
 {
     // the Voronoi instantiation carries no radical code, and one without
     // Weinberg records none of their code: those pointers are compile-time
@@ -1066,7 +1110,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G>
     __shared__ SL<G, S, MAXP, RAD> shv[Gw<G>::CPW];
     const int lane = __lane_id();
     const int gl = lane % G, gb = lane - gl;
-    const uint32_t below = (1u << gl) - 1u;
     SL<G, S, MAXP, RAD> &sh = shv[lane / G];
     uint32_t cnt[2] = {0, 0};  // candidates, vertex tests
     const int ncell = A.ncell;
@@ -1075,7 +1118,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G>
     if (gl < DC_N) sh.gs.cnt[gl] = 0;
     sh.gs.cell = 0;
     sh.gs.cend = 0;
-    sh.gs.tcur = -1;
     lds_fence();
 #ifdef VC_PHASE_CLOCKS
     // wave-level shader-clock cycles and executions of each phase body
@@ -1097,39 +1139,39 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G>
     } while (0)
 #endif
     for (;;) {
-        const bool r_new = VC_PHASE_RAN(PH_NEW);
-        if (c.phase == PH_NEW) {
-            if (cnt[1] > (1u << 30) || sh.gs.cnt[DC_NEWV] > (1u << 30) || sh.gs.cnt[DC_LOADED] > (1u << 30))
-                flush_counters<G, S, MAXP, RAD>(A, sh, cnt[0], cnt[1], gl);
-            ph_new<G, S, MAXP, F32, RAD>(A, sh, c, ncell, gl, gb);
-        }
-        VC_PHASE_MARK(0, r_new);
-        if (!__ballot(c.phase != PH_DONE)) break;
+        if (c.phase == PH_NEW &&
+            (cnt[1] > (1u << 30) || sh.gs.cnt[DC_NEWV] > (1u << 30) || sh.gs.cnt[DC_LOADED] > (1u << 30)))
+            flush_counters<G, S, MAXP, RAD>(A, sh, cnt[0], cnt[1], gl);
         // each cell that needs particles searches until it has a batch to
         // test or its search has ended
-        for (unsigned long long need = __builtin_amdgcn_ballot_w64(c.phase == PH_GATHER || c.phase == PH_BATCH); need;) {
+        for (unsigned long long need = __builtin_amdgcn_ballot_w64(c.phase <= PH_BATCH && c.phase >= 0); need;) {
             const int l0 = __builtin_ctzll(need) & ~(G - 1);
             need &= ~((unsigned long long)Gw<G>::FULL << l0);
             SL<G, S, MAXP, RAD> &sg = shv[l0 / G];
+            int ph = __builtin_amdgcn_readlane(c.phase, l0), bn = 0;
+            if (ph == PH_NEW) {
+                ph = co_new<G, S, MAXP, F32, RAD>(A, sg, c, ncell, opaque(lane), gb == l0);
+                VC_PHASE_MARK(0, true);
+            }
             const double lim = readlane_f64(c.lim, l0);
             const uint32_t rk = (uint32_t)__builtin_amdgcn_readlane((int)c.rk, l0);
-            int ph = __builtin_amdgcn_readlane(c.phase, l0), bn = 0;
-            do {
+            while (ph == PH_GATHER || ph == PH_BATCH) {
                 if (ph == PH_GATHER) {
-                    ph = co_gather<G, S, MAXP, RAD>(A, sg, lane, lim);
+                    ph = co_gather<G, S, MAXP, RAD>(A, sg, opaque(lane), lim);
                     VC_PHASE_MARK(1, true);
                 }
                 if (ph == PH_BATCH) {
-                    ph = co_batch<G, S, MAXP, F32, RAD>(A, sg, lane, lim, rk, bn);
+                    ph = co_batch<G, S, MAXP, F32, RAD>(A, sg, opaque(lane), lim, rk, bn);
                     VC_PHASE_MARK(2, true);
                 }
-            } while (ph == PH_GATHER || ph == PH_BATCH);
+            }
             if (gb == l0) {
                 c.phase = ph;
                 c.bn = bn;
                 c.bk = 0;
             }
         }
+        if (!__builtin_amdgcn_ballot_w64(c.phase != PH_DONE)) break;
 #ifdef VC_PHASE_CLOCKS
         const uint32_t t_cand = cnt[0];
 #endif
@@ -1139,15 +1181,27 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G>
 #endif
         VC_PHASE_MARK(3, true);
         // cuts and statistics wait until no group can advance without one
-        if (!__ballot(c.phase == PH_NEW || c.phase == PH_GATHER || c.phase == PH_BATCH || c.phase < 0)) {
+        if (!__ballot(c.phase <= PH_BATCH)) {
             const bool r_cut = VC_PHASE_RAN(PH_CUT);
-            if (c.phase == PH_CUT) ph_cut<G, S, MAXP, F32, RAD>(A, sh, c, cnt, gl, gb, below);
+            if (c.phase == PH_CUT) {
+                // (only the radical form gains by giving up its lane constants here)
+                const int l = RAD ? opaque(lane) : lane, gl = l % G, gb = l - gl;
+                ph_cut<G, S, MAXP, F32, RAD>(A, shv[l / G], c, cnt, gl, gb, (1u << gl) - 1u);
+            }
             VC_PHASE_MARK(4, r_cut);
             const bool r_st = VC_PHASE_RAN(PH_STATS);
-            if (c.phase == PH_STATS) ph_stats<G, S, MAXP, F32, RAD>(A, sh, c, cnt, gl, gb, below);
+            if (c.phase == PH_STATS) {
+                const int l = opaque(lane), gl = l % G, gb = l - gl;
+                SL<G, S, MAXP, RAD> &sh = shv[l / G];
+                ph_stats<G, S, MAXP, F32, RAD>(A, sh, c, cnt, gl, gb, (1u << gl) - 1u);
+            }
             VC_PHASE_MARK(5, r_st);
         }
-        if (c.phase < 0) cell_fail<G, S, MAXP, F32, RAD>(A, sh, c, -c.phase, gl);
+        if (c.phase < 0) {
+            const int l = opaque(lane), gl = l % G;
+            SL<G, S, MAXP, RAD> &sh = shv[l / G];
+            cell_fail<G, S, MAXP, F32, RAD>(A, sh, c, -c.phase, gl);
+        }
         VC_PHASE_MARK(7, true);
     }
     flush_counters<G, S, MAXP, RAD>(A, sh, cnt[0], cnt[1], gl);

@@ -99,6 +99,7 @@ struct CellArgs {
     int vcap;                  // > 0: a cell with more live vertices moves to the spill pass
     double tau;                // FP64 band, relative
     float tau32;               // FP32 band of the filter, relative
+    double kband32;            // its ratio to the FP64 band, with room for the rounding
     const double *rad;         // radii by sorted index (radical tessellation), or NULL
     const double *rmax;        // largest radius (device scalar)
     uint32_t mask;             // statistics mask
