@@ -161,7 +161,7 @@ typedef struct {
     int precision;       /* VC_FP64 or VC_F32_FILTER */
     int slots;           /* triangles per lane in the main cell kernel (2 or 4); 0: auto */
     int waves;           /* resident cell waves launched; 0: auto */
-    int chunk;           /* cells taken per work-queue grab; 0: auto */
+    int chunk;           /* cells taken per work-queue grab; 0: auto (by the number of cells) */
     int cells_per_wave;  /* cells sharing one wavefront: 1, 2 or 4; 0: 1 */
     double clip;         /* > 0: every cell starts as the cube (square) of this side
                             centred on its particle, cut to the box (section 3.1.3:
@@ -416,7 +416,8 @@ vc_status vc_device_fma_rate(int precision, int reps, void *stream, double *tflo
  *   of *opt (a coordinate outside it marks every cell VC_CELL_RANGE, on the
  *   device: the call does not synchronise); the grid of *opt may hold at
  *   most 65536 blocks; no radii.  Launch fields of *opt are used as by
- *   vc_container_create (waves capped at 512).
+ *   vc_container_create (waves of the forms that decide exactly in the main
+ *   kernel, one cell per wavefront and 2D, capped at 512).
  *   vol (n), cen (3n), nv, ne (n), fo (n x VC_FO_LEN): written when non-NULL;
  *   nf (n) and status (n) are required.  Fields are indexed by input order
  *   and equal those of vc_compute with the same options.

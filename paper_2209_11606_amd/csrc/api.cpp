@@ -200,9 +200,38 @@ void set_bands(CellArgs &A, int force)
 }
 
 struct Launch {
-    int slots = 2, waves = 0, chunk = 4, cpw = 1;
+    int slots = 2, waves = 0, chunk = 0, cpw = 1;  // chunk 0: by the number of cells
     int vcap = 0;  // vertex capacity before the spill pass (0: the kernel's own)
 };
+
+// Cells per queue grab of a wave, and waves that find a cell, for ncell
+// cells.  Sets of fewer cells than waves go one cell to a wave (1,000 walled
+// cells at one per wave: 0.40 ms a step with grabs of four, 0.24 with one;
+// 4,000 at two per wave: 0.28 against 0.32 with both groups filled), in 2D to
+// one for each group.  Beyond that every group has a cell, and a wave makes at
+// least four grabs of at most two cells for each group: longer ones leave
+// tails (10^6 periodic cells at two per wave: grabs of two to eight cells
+// within 1%, 16 +2%, 32 +6%).
+void fit_launch(int64_t ncell, int dim, int per_wave, int &waves, int &chunk)
+{
+    if (chunk <= 0) {
+        const int64_t low = dim == 2 || ncell > waves ? per_wave : 1;
+        chunk = (int)std::max(low, std::min<int64_t>(2 * per_wave, ncell / ((int64_t)waves * 4)));
+    } else {
+        chunk = (int)std::min<int64_t>((int64_t)chunk * per_wave, INT32_MAX / 2);
+    }
+    waves = (int)std::max<int64_t>(1, std::min<int64_t>(waves, (ncell + chunk - 1) / chunk));
+}
+
+hipError_t launch_main(CellArgs A, int dim, int precision, const Launch &L, int max_waves, hipStream_t s)
+{
+    int waves = std::min(L.waves, max_waves);
+    A.chunk = L.chunk;
+    fit_launch(A.ncell, dim, dim == 2 ? 8 : L.cpw, waves, A.chunk);
+    if (dim == 2) return launch_cells2d(A, precision, waves, s);
+    if (L.cpw > 1) return launch_cells_group(A, precision, L.cpw, waves, s);
+    return launch_cells(A, precision, L.slots, waves, s);
+}
 
 }  // namespace
 
@@ -380,7 +409,7 @@ vc_status create_common(vc_container *c, const double *xyz, const int64_t *offse
     c->precision = opts[0].precision;
     c->force = opts[0].force;
     c->launch.slots = opts[0].slots > 0 ? opts[0].slots : 2;
-    c->launch.chunk = opts[0].chunk > 0 ? opts[0].chunk : 4;
+    c->launch.chunk = opts[0].chunk;
     c->launch.cpw = opts[0].cells_per_wave > 0 ? opts[0].cells_per_wave : 1;
     c->launch.vcap = opts[0].capacity;
     int cu = device_cu_count();
@@ -458,7 +487,6 @@ CellArgs cell_args(const vc_container *c, const vc_result *r)
     A.cell_list = nullptr;
     A.ncell_dev = nullptr;
     A.queue = c->queue;
-    A.chunk = c->launch.chunk;
     set_bands(A, c->force);
     A.mask = r->mask;
     A.vol = r->vol;
@@ -519,7 +547,6 @@ vc_status enqueue_compute(vc_container *c, vc_result *r, hipStream_t s, bool eve
                           const int32_t *cell_list = nullptr, int ncell = -1, bool compact_subset = false)
 {
     CellArgs A = cell_args(c, r);
-    A.chunk = L.chunk;
     A.vcap = L.vcap;
     if (cell_list) {
         A.cell_list = cell_list;
@@ -528,9 +555,7 @@ vc_status enqueue_compute(vc_container *c, vc_result *r, hipStream_t s, bool eve
     HIP_TRY(launch_fill_i32(c->queue, 8, 0, s));
     HIP_TRY(launch_fill_i32((int32_t *)r->diag, VC_DIAG_LEN * 2, 0, s));
     if (events) HIP_TRY(hipEventRecord(r->ev0, s));
-    if (c->dim == 2) HIP_TRY(launch_cells2d(A, c->precision, std::min(L.waves, c->max_waves), s));
-    else if (L.cpw > 1) HIP_TRY(launch_cells_group(A, c->precision, L.cpw, std::min(L.waves, c->max_waves), s));
-    else HIP_TRY(launch_cells(A, c->precision, L.slots, std::min(L.waves, c->max_waves), s));
+    HIP_TRY(launch_main(A, c->dim, c->precision, L, c->max_waves, s));
     if (events) HIP_TRY(hipEventRecord(r->ev1, s));
     HIP_TRY(enqueue_spill(c, A, L.cpw, s));
     if (events) HIP_TRY(hipEventRecord(r->ev2, s));
@@ -1056,8 +1081,7 @@ vc_status slab_pass(const double *dxyz, int64_t n, const vc_options &opt, const 
             if (cert) A.lim_out = B.lim;
             const Launch &L = c->launch;
             HIP_TRY(launch_fill_i32(c->queue, 8, 0, s));
-            if (L.cpw > 1) HIP_TRY(launch_cells_group(A, c->precision, L.cpw, std::min(L.waves, c->max_waves), s));
-            else HIP_TRY(launch_cells(A, c->precision, L.slots, std::min(L.waves, c->max_waves), s));
+            HIP_TRY(launch_main(A, 3, c->precision, L, c->max_waves, s));
             HIP_TRY(enqueue_spill(c, A, L.cpw, s));
             if (cert)
                 HIP_TRY(launch_slab_cert(c->part, B.list, nl, B.lim, zlo, zhi, G.per[2] ? G.L[2] : 0.0,
@@ -1450,7 +1474,6 @@ vc_status vc_tessellate_noalloc(const double *xyz, int64_t n, const vc_options *
     A.off_radius = kOffRadius;
     A.ncell = (int)n;
     A.queue = queue;
-    A.chunk = opt->chunk > 0 ? opt->chunk : 4;
     A.vcap = opt->capacity;
     set_bands(A, opt->force);
     A.mask = (vol ? VC_VOLUME : 0) | (cen ? VC_CENTROID : 0) | (nv || ne ? VC_COUNTS : 0) | (fo ? VC_FACE_ORDERS : 0) |
@@ -1467,11 +1490,15 @@ vc_status vc_tessellate_noalloc(const double *xyz, int64_t n, const vc_options *
     A.diag = diag;
     A.xscratch = xs;
     A.xscratch_len = kNaXLen;
-    const int waves = std::min(opt->waves > 0 ? opt->waves : kNaWaves, kNaWaves);
-    const int cpw = opt->cells_per_wave > 0 ? opt->cells_per_wave : 1;
-    if (opt->dim == 2) HIP_TRY(launch_cells2d(A, opt->precision, waves, s));
-    else if (cpw > 1) HIP_TRY(launch_cells_group(A, opt->precision, cpw, waves, s));
-    else HIP_TRY(launch_cells(A, opt->precision, opt->slots > 0 ? opt->slots : 2, waves, s));
+    Launch L;
+    L.slots = opt->slots > 0 ? opt->slots : 2;
+    L.waves = opt->waves > 0 ? opt->waves : kNaWaves;
+    L.chunk = opt->chunk;
+    const int cpw = L.cpw = opt->cells_per_wave > 0 ? opt->cells_per_wave : 1;
+    // (the grouped kernel takes no exact-predicate workspace)
+    const bool grouped = opt->dim == 3 && cpw > 1;
+    if (grouped && opt->waves <= 0) L.waves = device_cu_count() * (cpw == 2 ? 20 : 16);
+    HIP_TRY(launch_main(A, opt->dim, opt->precision, L, grouped ? L.waves : kNaWaves, s));
     // the passes after the main one, as for a container
     CellArgs B = A;
     B.cell_list = spill;

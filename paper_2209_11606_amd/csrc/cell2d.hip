@@ -757,13 +757,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 #pragma unroll
     for (int k = 0; k < DC_N; k++) cnt[k] = 0;
     const int ncell = A.ncell_dev ? *A.ncell_dev : A.ncell;
-    for (;;) {
-        int base = 0;
-        if (gl == 0) base = atomicAdd(A.queue, A.chunk);
-        base = __shfl(base, gb);
-        if (base >= ncell) break;
-        int end = min(base + A.chunk, ncell);
-        for (int ci = base; ci < end; ci++) {
+    // a wave's groups take its cells in turn
+    for (Claim q = first_claim(A, ncell); q.cell < q.end || claim(A, q, ncell); q.cell = q.end) {
+        for (int ci = q.cell + lane / G; ci < q.end; ci += 64 / G) {
             int si = A.cell_list ? A.cell_list[ci] : ci;
             int st = poly_run<G, S, MAXL, F32>(A, sh, si, ws, cnt, lane, gl, gb);
             if (st != ST_OK && A.fo)

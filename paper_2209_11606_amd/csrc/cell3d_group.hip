@@ -177,7 +177,6 @@ struct GState {
     double ri;              // the particle's radius (radical tessellation), else 0
     int cur;                // next offset index
     int gtot, gc0;          // candidates of the gather, next batch start
-    int cell, cend;         // claimed range of the work queue
     int tess;               // its tessellation
     uint32_t cnt[DC_N];     // counters other than candidates and tests
 };
@@ -341,19 +340,11 @@ typedef const __attribute__((address_space(4))) Particle *ParticleConst;
 // ---- NEW: claim the next cell and set up the box (Eq. 1-2) ----
 // Returns the next phase; `in`: the lanes of the cell's group.
 template <int G, int S, int MAXP, bool F32, bool RAD>
-__device__ __forceinline__ int co_new(const CellArgs &A, SL<G, S, MAXP, RAD> &sh, SCell<S, F32> &c, int ncell, int lane,
-                                      bool in)
+__device__ __forceinline__ int co_new(const CellArgs &A, SL<G, S, MAXP, RAD> &sh, SCell<S, F32> &c, Claim &q, int ncell,
+                                      int lane, bool in)
 {
-    int cell = __builtin_amdgcn_readfirstlane(sh.gs.cell), cend = __builtin_amdgcn_readfirstlane(sh.gs.cend);
-    if (cell >= cend) {
-        int base = 0;
-        if (lane == 0) base = atomicAdd(A.queue, A.chunk);
-        cell = __builtin_amdgcn_readfirstlane(base);
-        cend = min(cell + A.chunk, ncell);
-        if (cell >= cend) return PH_DONE;
-        sh.gs.cend = cend;
-    }
-    sh.gs.cell = cell + 1;
+    if (q.cell >= q.end && !claim(A, q, ncell)) return PH_DONE;
+    const int cell = q.cell++;
     const int si = A.cell_list ? __builtin_amdgcn_readfirstlane(A.cell_list[cell]) : cell;
     ParticleConst me = (ParticleConst)(uintptr_t)(A.part + si);
     const double p[3] = {me->x, me->y, me->z};
@@ -545,10 +536,10 @@ __device__ __forceinline__ int co_batch(const CellArgs &A, SL<G, S, MAXP, RAD> &
     if (valid) {
         const int idx = sh.u.w.coff[b] + ci;
         code = sh.u.w.ccode[b];
-        const Particle q = A.part[idx];
-        a0 = q.x - sh.gs.p[0];
-        a1 = q.y - sh.gs.p[1];
-        a2 = q.z - sh.gs.p[2];
+        const Particle o = A.part[idx];
+        a0 = o.x - sh.gs.p[0];
+        a1 = o.y - sh.gs.p[1];
+        a2 = o.z - sh.gs.p[2];
         if (code != kNoShift) {
             TessConst T = (TessConst)(uintptr_t)(A.tess + __builtin_amdgcn_readfirstlane(sh.gs.tess));
             const int s0 = code % 5 - 2, s1 = code / 5 % 5 - 2, s2 = code / 25 - 2;
@@ -557,7 +548,7 @@ __device__ __forceinline__ int co_batch(const CellArgs &A, SL<G, S, MAXP, RAD> &
             if (s2) a2 = a2 + s2 * T->G.L[2];
         }
         d2 = a0 * a0 + a1 * a1 + a2 * a2;
-        pid = q.id;
+        pid = o.id;
         if (A.rad) {
             // radical plane (section 2.1.1): |x|^2 - ri^2 <= |x - q|^2 - rj^2
             h = 0.5 * (d2 + radical_shift(sh.gs.ri, A.rad[idx]));
@@ -1116,8 +1107,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G,
     SCell<S, F32> c;
     c.phase = PH_NEW;
     if (gl < DC_N) sh.gs.cnt[gl] = 0;
-    sh.gs.cell = 0;
-    sh.gs.cend = 0;
+    Claim q = first_claim(A, ncell);
     lds_fence();
 #ifdef VC_PHASE_CLOCKS
     // wave-level shader-clock cycles and executions of each phase body
@@ -1150,7 +1140,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G,
             SL<G, S, MAXP, RAD> &sg = shv[l0 / G];
             int ph = __builtin_amdgcn_readlane(c.phase, l0), bn = 0;
             if (ph == PH_NEW) {
-                ph = co_new<G, S, MAXP, F32, RAD>(A, sg, c, ncell, opaque(lane), gb == l0);
+                ph = co_new<G, S, MAXP, F32, RAD>(A, sg, c, q, ncell, opaque(lane), gb == l0);
                 VC_PHASE_MARK(0, true);
             }
             const double lim = readlane_f64(c.lim, l0);

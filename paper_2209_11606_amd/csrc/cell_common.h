@@ -391,6 +391,40 @@ __device__ __forceinline__ double radical_shift(double ri, double rj)
 #pragma clang fp contract(fast)
 
 // ---------------------------------------------------------------------------
+// Work queue.  A wave (one per workgroup) takes ranges of A.chunk cells: its
+// first by its number, the later ones from the queue, which hands out what is
+// beyond the first ranges.  The queue is one address for the whole chip and
+// serves about 85 million atomics a second (10^6 cells at two per wave take
+// 11.8 ms a step with one atomic each, 8.7 with one for four), and at the start
+// of a launch every wave wants one, so a wave takes one for all its groups of
+// lanes, none for its first range, and none at all where the first ranges
+// cover every cell (4,000 cells at two per wave: 0.35 -> 0.28 ms a step).
+// ---------------------------------------------------------------------------
+struct Claim {
+    int cell, end;  // wave-uniform
+};
+
+__device__ __forceinline__ Claim first_claim(const CellArgs &A, int ncell)
+{
+    const int64_t b = (int64_t)blockIdx.x * A.chunk;
+    return Claim{(int)(b < ncell ? b : ncell), (int)(b + A.chunk < ncell ? b + A.chunk : ncell)};
+}
+
+// the next range; false when no cell is left
+__device__ __forceinline__ bool claim(const CellArgs &A, Claim &q, int ncell)
+{
+    const int64_t stat = (int64_t)gridDim.x * A.chunk;
+    if (stat >= ncell) return false;
+    int base = 0;
+    if (__lane_id() == 0) base = atomicAdd(A.queue, A.chunk);
+    const int64_t b = stat + __builtin_amdgcn_readfirstlane(base);
+    if (b >= ncell) return false;
+    q.cell = (int)b;
+    q.end = (int)(b + A.chunk < ncell ? b + A.chunk : ncell);
+    return true;
+}
+
+// ---------------------------------------------------------------------------
 // Wave helpers.  Reductions and scans use DPP lane movement (quad
 // permutations, row mirrors, row shifts and the row broadcasts of the
 // 64-wide wave) and end with a readlane, so the result is wave-uniform and
