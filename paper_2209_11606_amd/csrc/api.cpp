@@ -211,24 +211,37 @@ struct Launch {
 // one for each group.  Beyond that every group has a cell, and a wave makes at
 // least four grabs of at most two cells for each group: longer ones leave
 // tails (10^6 periodic cells at two per wave: grabs of two to eight cells
-// within 1%, 16 +2%, 32 +6%).
+// within 1%, 16 +2%, 32 +6%).  The 2D lane kernel always fills its 64 lanes
+// (100,000 cells: 0.53 ms a step against 0.70 with 24 lanes in use).
 void fit_launch(int64_t ncell, int dim, int per_wave, int &waves, int &chunk)
 {
     if (chunk <= 0) {
-        const int64_t low = dim == 2 || ncell > waves ? per_wave : 1;
-        chunk = (int)std::max(low, std::min<int64_t>(2 * per_wave, ncell / ((int64_t)waves * 4)));
+        const int64_t low = dim == 2 || ncell > waves ? per_wave : 1, high = per_wave == 64 ? 64 : 2 * per_wave;
+        chunk = (int)std::max(low, std::min<int64_t>(high, ncell / ((int64_t)waves * 4)));
     } else {
         chunk = (int)std::min<int64_t>((int64_t)chunk * per_wave, INT32_MAX / 2);
     }
     waves = (int)std::max<int64_t>(1, std::min<int64_t>(waves, (ncell + chunk - 1) / chunk));
 }
 
-hipError_t launch_main(CellArgs A, int dim, int precision, const Launch &L, int max_waves, hipStream_t s)
+// 2D sets of this many particles and more are computed one cell per lane, the
+// others eight lanes per cell: a wave of the lane kernel takes long however few
+// cells there are.  Steps by eight lanes and by lane: 20,000 cells 0.41 and 0.44
+// ms, 60,000 0.55 and 0.49, 100,000 0.67 and 0.52, 10^6 3.2 and 1.77; radical
+// 40,000 0.53 and 0.56, 100,000 0.71 and 0.66, 10^6 3.8 and 3.1.  One line for
+// both, since equal radii give the Voronoi cells bit for bit.  The container's
+// size decides, so that a subset's cells are those of the whole set; a vertex
+// capacity asks for the kernel whose slots it limits.
+constexpr int64_t kLaneCells = 80000;
+
+bool cells_by_lane(int dim, int64_t n, int vcap) { return dim == 2 && vcap == 0 && n >= kLaneCells; }
+
+hipError_t launch_main(CellArgs A, int dim, int precision, const Launch &L, int max_waves, bool by_lane, hipStream_t s)
 {
     int waves = std::min(L.waves, max_waves);
     A.chunk = L.chunk;
-    fit_launch(A.ncell, dim, dim == 2 ? 8 : L.cpw, waves, A.chunk);
-    if (dim == 2) return launch_cells2d(A, precision, waves, s);
+    fit_launch(A.ncell, dim, by_lane ? 64 : dim == 2 ? 8 : L.cpw, waves, A.chunk);
+    if (dim == 2) return launch_cells2d(A, precision, by_lane, waves, s);
     if (L.cpw > 1) return launch_cells_group(A, precision, L.cpw, waves, s);
     return launch_cells(A, precision, L.slots, waves, s);
 }
@@ -265,9 +278,10 @@ struct vc_container {
     Offset *offs = nullptr;
     int noff = 0;
     int32_t *queue = nullptr;    // [0]: main queue head, [1]: spill queue head, [2]: spill count,
-                                 // [3..5]: the Weinberg code kernels' heads and list count
+                                 // [3..5]: the Weinberg code kernels' heads and list count,
+                                 // [6..7]: head and count of spill_list2
     int32_t *spill_list = nullptr;
-    int32_t *spill_list2 = nullptr;  // 3D: overflows of the first spill pass
+    int32_t *spill_list2 = nullptr;  // 3D: overflows of the first spill pass; 2D: cells the lane kernel leaves
     int32_t *sample_list = nullptr;  // tuning sample (batches)
     int nsample = 0;
     double *xscratch = nullptr;
@@ -458,7 +472,7 @@ vc_status create_common(vc_container *c, const double *xyz, const int64_t *offse
     TRY(dalloc(&c->offs, offs.size()));
     TRY(dalloc(&c->queue, 8));
     TRY(dalloc(&c->spill_list, (size_t)c->n));
-    if (dim == 3) TRY(dalloc(&c->spill_list2, (size_t)c->n));
+    TRY(dalloc(&c->spill_list2, (size_t)c->n));
     TRY(dalloc(&c->xscratch, (size_t)c->max_waves * c->xscratch_len));
 #undef TRY
     HIP_TRY(hipMemcpyAsync(c->tess, c->htess.data(), c->htess.size() * sizeof(Tess), hipMemcpyHostToDevice, s));
@@ -501,6 +515,9 @@ CellArgs cell_args(const vc_container *c, const vc_result *r)
     A.status = r->status;
     A.spill_list = c->spill_list;
     A.spill_count = c->queue + 2;
+    A.left_list = c->spill_list2;
+    A.left_queue = c->queue + 6;
+    A.left_count = c->queue + 7;
     A.diag = r->diag;
     A.xscratch = c->xscratch;
     A.xscratch_len = c->xscratch_len;
@@ -555,7 +572,7 @@ vc_status enqueue_compute(vc_container *c, vc_result *r, hipStream_t s, bool eve
     HIP_TRY(launch_fill_i32(c->queue, 8, 0, s));
     HIP_TRY(launch_fill_i32((int32_t *)r->diag, VC_DIAG_LEN * 2, 0, s));
     if (events) HIP_TRY(hipEventRecord(r->ev0, s));
-    HIP_TRY(launch_main(A, c->dim, c->precision, L, c->max_waves, s));
+    HIP_TRY(launch_main(A, c->dim, c->precision, L, c->max_waves, cells_by_lane(c->dim, c->n, L.vcap), s));
     if (events) HIP_TRY(hipEventRecord(r->ev1, s));
     HIP_TRY(enqueue_spill(c, A, L.cpw, s));
     if (events) HIP_TRY(hipEventRecord(r->ev2, s));
@@ -1081,7 +1098,7 @@ vc_status slab_pass(const double *dxyz, int64_t n, const vc_options &opt, const 
             if (cert) A.lim_out = B.lim;
             const Launch &L = c->launch;
             HIP_TRY(launch_fill_i32(c->queue, 8, 0, s));
-            HIP_TRY(launch_main(A, 3, c->precision, L, c->max_waves, s));
+            HIP_TRY(launch_main(A, 3, c->precision, L, c->max_waves, false, s));
             HIP_TRY(enqueue_spill(c, A, L.cpw, s));
             if (cert)
                 HIP_TRY(launch_slab_cert(c->part, B.list, nl, B.lim, zlo, zhi, G.per[2] ? G.L[2] : 0.0,
@@ -1487,6 +1504,9 @@ vc_status vc_tessellate_noalloc(const double *xyz, int64_t n, const vc_options *
     A.status = status;
     A.spill_list = spill;
     A.spill_count = queue + 2;
+    A.left_list = reinterpret_cast<int32_t *>(b + kNaSpill2);
+    A.left_queue = queue + 6;
+    A.left_count = queue + 7;
     A.diag = diag;
     A.xscratch = xs;
     A.xscratch_len = kNaXLen;
@@ -1498,7 +1518,8 @@ vc_status vc_tessellate_noalloc(const double *xyz, int64_t n, const vc_options *
     // (the grouped kernel takes no exact-predicate workspace)
     const bool grouped = opt->dim == 3 && cpw > 1;
     if (grouped && opt->waves <= 0) L.waves = device_cu_count() * (cpw == 2 ? 20 : 16);
-    HIP_TRY(launch_main(A, opt->dim, opt->precision, L, grouped ? L.waves : kNaWaves, s));
+    HIP_TRY(launch_main(A, opt->dim, opt->precision, L, grouped ? L.waves : kNaWaves,
+                        cells_by_lane(opt->dim, n, opt->capacity), s));
     // the passes after the main one, as for a container
     CellArgs B = A;
     B.cell_list = spill;

@@ -11,6 +11,8 @@
 // first vertex (a, .) and last vertex (., b) give the two new vertices
 // (a, p) and (p, b).  Side decisions as in 3D: FP64 (or FP32 with an FP64
 // recheck) outside a band, exact inside it.
+#include <algorithm>
+
 #include "cell_common.h"
 
 namespace vc {
@@ -801,9 +803,602 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     }
 }
 
+// ---------------------------------------------------------------------------
+// The main 2D kernel: one cell per lane.  A planar cell takes some fifty
+// particles, ten cuts and six vertices, too little work to share a cell's steps
+// over lanes: in the kernel above each of its eight lanes per cell runs every
+// step's control.  Here 64 cells share each instruction, and the wave alternates
+// between two loops: every lane takes its next particles until one may cut its
+// cell (a maximum over the vertices of the side value, not below the band),
+// then the lanes that have such a particle cut together.
+//
+// The polygon is a ring of kLaneV slots in counter-clockwise order with holes:
+// vertex coordinates in registers (a hole is the particle, 0, which no bisector
+// cuts off), a live mask, and for each slot the place in LDS of the line its
+// entering edge lies on.  A line is kept as a reference (particle and image, or
+// wall) and its coefficients are computed again when a cut or the statistics
+// need them.  A cut keeps the first removed slot for its first new vertex and
+// the last for its second; when it removes a single vertex, the slots up to the
+// next hole move by one.  A cell that outgrows the ring or searches past the
+// offset list is left to the kernel above, as part of the main pass.  Bound by
+// instruction issue and by the particle loads' latency (457 VALU instructions a
+// cell, VALU busy 56%); periodic 10^6 cells: 1.33 ms where the kernel above
+// takes 2.85.
+// ---------------------------------------------------------------------------
+constexpr int kLaneV = 12;
+
+typedef const __attribute__((address_space(4))) Tess *TessConst2;
+
+constexpr int kLaneB = 12;  // blocks a lane gathers at once
+// The wave turns from particles to cuts once the lanes that wait are half as
+// many as those that go on (10^6 periodic cells, step: waiting for all lanes
+// 3.13 ms, half of the lanes 1.79, a third 1.75, a fifth 1.78).
+constexpr int kLaneWait = 2;
+
+struct LaneLds {
+    int32_t li[kLaneV][64];   // lines: sorted particle index, or the (negative) wall label
+    int32_t cur[kLaneB][64];  // gathered blocks: first particle, end, image code
+    int32_t end[kLaneB][64];
+    uint8_t lc[kLaneV][64];   // lines: image code
+    uint8_t code[kLaneB][64];
+    int32_t offs[96];         // the offset list: dx + 8 | dy + 8 << 8 | m << 16
+};
+
+struct Line {
+    double n0, n1, h;
+    int wall;
+};
+
+// bisector of the cell's particle and the particle at (x, y) moved by the
+// image code's periods
+template <bool RAD>
+__device__ __forceinline__ void lane_bisector(const CellArgs &A, TessConst2 T, double px, double py, double ri, double x,
+                                              double y, int code, int idx, double &q0, double &q1, double &d2, double &h)
+{
+    q0 = x - px;
+    q1 = y - py;
+    if (code != kNoShift) {
+        const int s0 = code % 5 - 2, s1 = code / 5 % 5 - 2;
+        if (s0) q0 = q0 + s0 * T->G.L[0];
+        if (s1) q1 = q1 + s1 * T->G.L[1];
+    }
+    d2 = fma(q0, q0, q1 * q1);
+    // radical line (section 2.1.1): |x|^2 - ri^2 <= |x - q|^2 - rj^2
+    h = RAD ? 0.5 * (d2 + radical_shift(ri, A.rad[idx])) : 0.5 * d2;
+}
+
+template <bool RAD>
+__device__ __forceinline__ Line lane_line(const CellArgs &A, TessConst2 T, double px, double py, double ri, int li, int code)
+{
+    Line r;
+    if (li >= 0) {
+        double d2;
+        lane_bisector<RAD>(A, T, px, py, ri, A.part[li].x, A.part[li].y, code, li, r.n0, r.n1, d2, r.h);
+        r.wall = 0;
+    } else {
+        // box walls -1..-4, clip walls -7..-10: face 2 d + side
+        const bool clip = li <= -7;
+        const int f = clip ? -li - 7 : -li - 1, side = f & 1;
+        const double sg = side ? 1.0 : -1.0;
+        r.n0 = f < 2 ? sg : 0.0;
+        r.n1 = f < 2 ? 0.0 : sg;
+        const double lo = f < 2 ? T->G.lo[0] : T->G.lo[1], hi = f < 2 ? T->G.hi[0] : T->G.hi[1], p = f < 2 ? px : py;
+        r.h = clip ? T->clip_half : (side ? hi - p : -(lo - p));
+        r.wall = 1;
+    }
+    return r;
+}
+
+// exact side of line p at the vertex of lines a and b
+template <bool RAD>
+__device__ __forceinline__ int lane_exact(const Line &a, double ra, const Line &b, double rb, const Line &p, double rp,
+                                          double ri, double *ws)
+{
+    const PlaneD pa = {a.n0, a.n1, 0.0, a.h, a.wall}, pb = {b.n0, b.n1, 0.0, b.h, b.wall}, pp = {p.n0, p.n1, 0.0, p.h, p.wall};
+    if (RAD) return exact_side2(PlaneR{pa, ri, ra}, PlaneR{pb, ri, rb}, PlaneR{pp, ri, rp}, ws);
+    return exact_side2(pa, pb, pp, ws);
+}
+
+// the live slot after slot i of the ring
+__device__ __forceinline__ int lane_next(uint32_t live, int i)
+{
+    const uint32_t up = live >> (i + 1);
+    return up ? i + 1 + __builtin_ctz(up) : __builtin_ctz(live);
+}
+
+// three waves per SIMD: at four the polygon and a cut's two lines spill (6.8
+// ms a step against 3.1 with every lane waiting), at two 3.2
+template <bool F32, bool RAD>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_cells2d_lane(CellArgs Ain)
+{
+    CellArgs A = Ain;
+    if (!RAD) A.rad = nullptr;
+    constexpr int V = kLaneV;
+    constexpr uint32_t ALL = (1u << V) - 1u;
+    __shared__ LaneLds sh;
+    const int lane = __lane_id();
+    double *ws = A.xscratch + (size_t)blockIdx.x * A.xscratch_len;
+    TessConst2 T = (TessConst2)(uintptr_t)A.tess;
+    const int noff = min(A.noff, 96);
+    for (int k = lane; k < noff; k += 64) sh.offs[k] = (A.offs[k].dx + 8) | (A.offs[k].dy + 8) << 8 | A.offs[k].m << 16;
+    lds_sync2();
+    const double tau = A.tau;
+    uint32_t ncand = 0, ntest = 0, ncut = 0, nexact = 0, nre = 0, nblk = 0, nload = 0;
+    const int ncell = A.ncell;
+    for (Claim cq = first_claim(A, ncell); cq.cell < cq.end || claim(A, cq, ncell);) {
+        const int ci = cq.cell + lane;
+        const bool act = ci < cq.end;
+        cq.cell = min(cq.cell + 64, cq.end);
+        int si = 0, id = 0;
+        double px = 0.0, py = 0.0, ri = 0.0;
+        if (act) {
+            si = A.cell_list ? A.cell_list[ci] : ci;
+            px = A.part[si].x;
+            py = A.part[si].y;
+            id = A.part[si].id;
+            if (RAD) ri = A.rad[si];
+        }
+        // the box (Eq. 1-2, clipped as in section 3.1.3): corners in slots
+        // 0, 3, 6, 9 entered by faces x-, y-, x+, y+
+        double vx[V], vy[V];
+        float fx[V], fy[V];
+#pragma unroll
+        for (int i = 0; i < V; i++) vx[i] = vy[i] = 0.0;
+        int bc[2], fl[2];
+        {
+            double off[4];
+#pragma unroll
+            for (int f = 0; f < 4; f++) {
+                const int d = f >> 1, side = f & 1;
+                const double p = d ? py : px;
+                off[f] = T->G.per[d] ? 0.5 * T->G.L[d] : (side ? T->G.hi[d] - p : -(T->G.lo[d] - p));
+                int li = T->G.per[d] ? si : -(f + 1);
+                int code = kNoShift;
+                if (T->G.per[d]) code += (side ? 1 : -1) * (d ? 5 : 1);
+                if (T->clip_half > 0.0 && T->clip_half < off[f]) {
+                    off[f] = T->clip_half;
+                    li = -(7 + f);
+                    code = kNoShift;
+                }
+                sh.li[f][lane] = li;
+                sh.lc[f][lane] = (uint8_t)code;
+            }
+            vx[0] = -off[0];
+            vy[0] = -off[2];
+            vx[3] = off[1];
+            vy[3] = -off[2];
+            vx[6] = off[1];
+            vy[6] = off[3];
+            vx[9] = -off[0];
+            vy[9] = off[3];
+#pragma unroll
+            for (int d = 0; d < 2; d++) {
+                const double p = d ? py : px;
+                const int k = min(max((int)floor((p - T->G.lo[d]) * T->G.inv_bs[d]), 0), T->G.g[d] - 1);
+                bc[d] = k;
+                fl[d] = (p - (T->G.lo[d] + k * T->G.bs[d])) * 2.0 > T->G.bs[d] ? -1 : 1;
+            }
+        }
+        // faces in LDS places 0: x-, 1: x+, 2: y-, 3: y+
+        unsigned long long ls = 0ull | (2ull << 12) | (1ull << 24) | (3ull << 36);
+        uint32_t live = 1u | (1u << 3) | (1u << 6) | (1u << 9), lused = 0xfu;
+        if (F32) {
+#pragma unroll
+            for (int i = 0; i < V; i++) {
+                fx[i] = (float)vx[i];
+                fy[i] = (float)vy[i];
+            }
+        }
+        double R2 = 0.0;
+#pragma unroll
+        for (int i = 0; i < V; i += 3) R2 = fmax(R2, vx[i] * vx[i] + vy[i] * vy[i]);
+        double R = sqrt(R2), lim = search_lim(R2, R, A, ri);
+        int o = 0, n = 4;
+        int st = act ? ST_OK : -1;
+        bool done = !act;
+        // the gathered blocks not yet opened, the open one's particles, and two
+        // particles loaded ahead (index -1: none)
+        int nb = 0, bi = 0, gcur = 0, gend = 0, gcode = kNoShift;
+        int i0 = -1, i1 = -1, c0 = kNoShift, c1 = kNoShift;
+        double x0 = 0.0, y0 = 0.0, x1 = 0.0, y1 = 0.0;
+        double q0 = 0.0, q1 = 0.0, h = 0.0, band = 0.0;  // the particle that may cut
+        int qi = 0, code = kNoShift;
+        for (;;) {
+            bool pend = false;
+            if (!__builtin_amdgcn_ballot_w64(!done)) break;
+            // ---- the next blocks within reach ----
+            if (!done && i0 < 0) {
+                nb = bi = 0;
+                const double bs2 = 0.25 * T->bsmin2;
+                while (nb < kLaneB) {
+                    if (o >= noff) {
+                        // past the offset list: the shell search is the
+                        // other kernel's
+                        if (nb == 0) {
+                            st = ST_CAP;
+                            done = true;
+                        }
+                        break;
+                    }
+                    const int w = sh.offs[o];
+                    if ((w >> 16) * bs2 >= lim) {
+                        if (nb == 0) done = true;
+                        break;
+                    }
+                    o++;
+                    const int dd[2] = {((w & 0xff) - 8) * fl[0], ((w >> 8 & 0xff) - 8) * fl[1]};
+                    int bb[2], sv[2];
+                    bool ok = true;
+                    double d2b = 0.0;
+#pragma unroll
+                    for (int d = 0; d < 2; d++) {
+                        const int g = T->G.g[d], b = bc[d] + dd[d];
+                        int u = b, s = 0;
+                        if (T->G.per[d]) {
+                            // one period at most where the axis has as many
+                            // blocks as the list reaches, else two
+                            const int rounds = g >= kOffRadius ? 1 : 3;
+                            for (int r = 0; r < rounds; r++) {
+                                const int v = u < 0 ? -1 : (u >= g ? 1 : 0);
+                                s += v;
+                                u -= v * g;
+                            }
+                            if (s > 2 || s < -2 || u < 0 || u >= g) ok = false;
+                        } else if (b < 0 || b >= g) {
+                            ok = false;
+                        }
+                        bb[d] = u;
+                        sv[d] = s;
+                        const double p = d ? py : px, blo = T->G.lo[d] + b * T->G.bs[d];
+                        const double e = fmax(0.0, fmax(blo - p, p - (blo + T->G.bs[d])));
+                        d2b += e * e;
+                    }
+                    if (ok && d2b < lim) {
+                        sh.cur[nb][lane] = T->bbase + bb[0] + T->G.g[0] * bb[1];
+                        sh.code[nb][lane] = (uint8_t)(25 * 2 + 5 * (sv[1] + 2) + (sv[0] + 2));
+                        nb++;
+                    }
+                }
+                nblk += nb;
+                // their particles' ranges, independent loads
+#pragma unroll 4
+                for (int k = 0; k < nb; k++) {
+                    const int blk = sh.cur[k][lane];
+                    const int s = A.start[blk], e = A.start[blk + 1];
+                    sh.cur[k][lane] = s;
+                    sh.end[k][lane] = e;
+                    nload += e - s;
+                }
+                gcur = gend = 0;
+            }
+            // two particles ahead
+#define VC_LANE_NEXT(I, CODE, X, Y)                              \
+    do {                                                         \
+        while (gcur >= gend && bi < nb) {                        \
+            gcur = sh.cur[bi][lane];                             \
+            gend = sh.end[bi][lane];                             \
+            gcode = sh.code[bi][lane];                           \
+            bi++;                                                \
+        }                                                        \
+        I = -1;                                                  \
+        if (gcur < gend) {                                       \
+            I = gcur++;                                          \
+            CODE = gcode;                                        \
+            X = A.part[I].x;                                     \
+            Y = A.part[I].y;                                     \
+        }                                                        \
+    } while (0)
+            if (!done && i0 < 0) {
+                VC_LANE_NEXT(i0, c0, x0, y0);
+                VC_LANE_NEXT(i1, c1, x1, y1);
+            }
+            // ---- particles, until one may cut ----
+            for (;;) {
+                const bool go = !done && !pend && i0 >= 0;
+                const int ngo = __popcll(__builtin_amdgcn_ballot_w64(go));
+                if (ngo == 0 || kLaneWait * __popcll(__builtin_amdgcn_ballot_w64(!done && !go)) >= ngo) break;
+                if (go) {
+                    const double x = x0, y = y0;
+                    qi = i0;
+                    code = c0;
+                    i0 = i1;
+                    c0 = c1;
+                    x0 = x1;
+                    y0 = y1;
+                    VC_LANE_NEXT(i1, c1, x1, y1);
+                    double d2;
+                    lane_bisector<RAD>(A, T, px, py, ri, x, y, code, qi, q0, q1, d2, h);
+                    if (d2 < lim && !(qi == si && code == kNoShift)) {
+                        ncand++;
+                        ntest += n;
+                        band = tau * ((fabs(q0) + fabs(q1)) * R + fabs(h));
+                        if (d2 == 0.0) {
+                            st = ST_DUP;
+                            done = true;
+                        } else if (F32) {
+                            const float g0 = (float)q0, g1 = (float)q1, gh = (float)h;
+                            const float band32 = A.tau32 * ((fabsf(g0) + fabsf(g1)) * ((float)R * 1.0000001f) + fabsf(gh));
+                            float m = -INFINITY;
+#pragma unroll
+                            for (int i = 0; i < V; i++) m = fmaxf(m, fmaf(g0, fx[i], fmaf(g1, fy[i], -gh)));
+                            pend = !(m < -band32);
+                        } else {
+                            double m = -INFINITY;
+#pragma unroll
+                            for (int i = 0; i < V; i++) m = fmax(m, fma(q0, vx[i], fma(q1, vy[i], -h)));
+                            pend = !(m < -band);
+                        }
+                    }
+                }
+            }
+#undef VC_LANE_NEXT
+            // ---- cuts ----
+            uint32_t C = 0, I = 0, Z = 0;
+            if (pend) {
+#pragma unroll
+                for (int i = 0; i < V; i++) {
+                    const double s = fma(q0, vx[i], fma(q1, vy[i], -h));
+                    C |= s > band ? 1u << i : 0u;
+                    I |= !(s > band) && !(s < -band) ? 1u << i : 0u;
+                }
+                C &= live;
+                I &= live;
+                if (F32) {
+                    // tests the FP32 band leaves to FP64 (the FP64 values
+                    // agree with the FP32 ones outside it)
+                    const float g0 = (float)q0, g1 = (float)q1, gh = (float)h;
+                    const float band32 = A.tau32 * ((fabsf(g0) + fabsf(g1)) * ((float)R * 1.0000001f) + fabsf(gh));
+                    uint32_t U = 0;
+#pragma unroll
+                    for (int i = 0; i < V; i++) {
+                        const float s = fmaf(g0, fx[i], fmaf(g1, fy[i], -gh));
+                        U |= !(s > band32) && !(s < -band32) ? 1u << i : 0u;
+                    }
+                    nre += __popc(U & live);
+                }
+            }
+            // in-band vertices: exact decisions, one lane at a time
+            for (unsigned long long m = __builtin_amdgcn_ballot_w64(I != 0); m; m &= m - 1) {
+                if (lane == __builtin_ctzll(m)) {
+                    const Line lp = {q0, q1, h, 0};
+                    const double rp = RAD ? A.rad[qi] : 0.0;
+                    for (uint32_t b = I; b; b &= b - 1) {
+                        const int i = __builtin_ctz(b), j = lane_next(live, i);
+                        const int pa = (int)(ls >> (4 * i)) & 15, pb = (int)(ls >> (4 * j)) & 15;
+                        const int la = sh.li[pa][lane], lb = sh.li[pb][lane];
+                        const Line a = lane_line<RAD>(A, T, px, py, ri, la, sh.lc[pa][lane]);
+                        const Line c = lane_line<RAD>(A, T, px, py, ri, lb, sh.lc[pb][lane]);
+                        const int sg = lane_exact<RAD>(a, RAD && la >= 0 ? A.rad[la] : 0.0, c,
+                                                       RAD && lb >= 0 ? A.rad[lb] : 0.0, lp, rp, ri, ws);
+                        if (sg > 0) C |= 1u << i;
+                        if (sg == 0) Z |= 1u << i;
+                        nexact++;
+                    }
+                }
+            }
+            if (RAD && C && !(live & ~C & ~Z)) {
+                // a radical line can leave no vertex strictly inside: empty cell
+                st = ST_EMPTY;
+                done = true;
+                C = 0;
+            }
+            if (C) {
+                // the removed run, turned so that it does not pass the ring's end
+                const uint32_t K = live & ~C;
+                const int k0 = K ? __builtin_ctz(K) : 0;
+                const uint32_t Cr = ((C >> k0) | (C << (V - k0))) & ALL, Kr = ((K >> k0) | (K << (V - k0))) & ALL;
+                const int f1 = __builtin_ctz(Cr), l1 = 31 - __builtin_clz(Cr);
+                const uint32_t between = ((1u << l1) - 1u) & ~((1u << f1) - 1u);
+                const int r = __popc(C);
+                if (!K || (Kr & between) || (r == 1 && n == V)) {
+                    // no kept vertex or more than one run (a broken polygon), or
+                    // no room: the other kernel's
+                    st = ST_CAP;
+                    done = true;
+                } else {
+                    const int f = f1 + k0 >= V ? f1 + k0 - V : f1 + k0, l = l1 + k0 >= V ? l1 + k0 - V : l1 + k0;
+                    const uint32_t up = Kr >> (l1 + 1);
+                    const int nr = up ? l1 + 1 + __builtin_ctz(up) : 0;
+                    const int nk = nr + k0 >= V ? nr + k0 - V : nr + k0;
+                    const int pa = (int)(ls >> (4 * f)) & 15, pb = (int)(ls >> (4 * nk)) & 15;
+                    const Line a = lane_line<RAD>(A, T, px, py, ri, sh.li[pa][lane], sh.lc[pa][lane]);
+                    const Line b = lane_line<RAD>(A, T, px, py, ri, sh.li[pb][lane], sh.lc[pb][lane]);
+                    const double La[3] = {a.n0, a.n1, a.h}, Lb[3] = {b.n0, b.n1, b.h}, Lp[3] = {q0, q1, h};
+                    double ax, ay, bx, by;
+                    cramer2(La, Lp, ax, ay);
+                    cramer2(Lp, Lb, bx, by);
+                    // lines of the removed vertices but the first are free
+                    for (uint32_t d = C & ~(1u << f); d; d &= d - 1) lused &= ~(1u << ((ls >> (4 * __builtin_ctz(d))) & 15));
+                    const int pl = __builtin_ctz(~lused);
+                    lused |= 1u << pl;
+                    sh.li[pl][lane] = qi;
+                    sh.lc[pl][lane] = (uint8_t)code;
+                    int g = l;
+                    uint32_t mv = 0;
+                    if (r == 1) {
+                        // the slots from f + 1 to the next hole z move by one
+                        g = f + 1 == V ? 0 : f + 1;
+                        const uint32_t hole = ~live & ALL;
+                        const uint32_t hr = ((hole >> g) | (hole << (V - g))) & ALL;
+                        const int cntm = __builtin_ctz(hr);  // slots g .. g + cntm - 1 are live
+                        const uint32_t mr = ((1u << cntm) - 1u) << 1;  // destinations, turned by g
+                        mv = ((mr << g) | (mr >> (V - g))) & ALL;
+                        for (int c = cntm; c > 0; c--) {
+                            const int to = g + c >= V ? g + c - V : g + c, from = to == 0 ? V - 1 : to - 1;
+                            ls = (ls & ~(15ull << (4 * to))) | (((ls >> (4 * from)) & 15ull) << (4 * to));
+                        }
+                        live |= mv;
+                    }
+                    ls = (ls & ~(15ull << (4 * g))) | ((unsigned long long)pl << (4 * g));
+                    live = (live & ~C) | (1u << f) | (1u << g);
+                    const uint32_t dead = C & ~live;
+                    const double wx = vx[V - 1], wy = vy[V - 1];
+#pragma unroll
+                    for (int i = V - 1; i >= 0; i--) {
+                        const bool m = (mv >> i) & 1, z = (dead >> i) & 1;
+                        double x = m ? (i ? vx[i ? i - 1 : 0] : wx) : vx[i], y = m ? (i ? vy[i ? i - 1 : 0] : wy) : vy[i];
+                        x = z ? 0.0 : x;
+                        y = z ? 0.0 : y;
+                        x = i == f ? ax : x;
+                        y = i == f ? ay : y;
+                        vx[i] = i == g ? bx : x;
+                        vy[i] = i == g ? by : y;
+                    }
+                    if (F32) {
+#pragma unroll
+                        for (int i = 0; i < V; i++) {
+                            fx[i] = (float)vx[i];
+                            fy[i] = (float)vy[i];
+                        }
+                    }
+                    n += 2 - r;
+                    ncut++;
+                    R2 = 0.0;
+#pragma unroll
+                    for (int i = 0; i < V; i++) R2 = fmax(R2, vx[i] * vx[i] + vy[i] * vy[i]);
+                    // a vertex that is not a number does not show in the maximum
+                    bool fin = R2 < 1e300 && ax == ax && ay == ay && bx == bx && by == by;
+                    R = sqrt(R2);
+                    lim = search_lim(R2, R, A, ri);
+                    if (A.vcap > 0 && n > A.vcap) fin = false;
+                    if (!fin) {
+                        st = ST_CAP;
+                        done = true;
+                    }
+                }
+            }
+        }
+        // ---- statistics: area, centroid, perimeter, edges, neighbours ----
+        const bool fin = st == ST_OK;
+        // edge from the vertex in slot i to the next: zero length when the
+        // vertex lies on the line that edge's end leaves by
+        uint32_t I = 0, zb = 0;
+        if (fin) {
+            for (uint32_t b = live; b; b &= b - 1) {
+                const int i = __builtin_ctz(b);
+                const int k = lane_next(live, lane_next(live, i)), pk = (int)(ls >> (4 * k)) & 15;
+                const Line c = lane_line<RAD>(A, T, px, py, ri, sh.li[pk][lane], sh.lc[pk][lane]);
+                double x = 0.0, y = 0.0;
+#pragma unroll
+                for (int j = 0; j < V; j++) {
+                    x = i == j ? vx[j] : x;
+                    y = i == j ? vy[j] : y;
+                }
+                const double sd = c.n0 * x + c.n1 * y - c.h;
+                const double bd = tau * ((fabs(c.n0) + fabs(c.n1)) * R + fabs(c.h));
+                if (!(sd < -bd)) I |= 1u << i;
+            }
+        }
+        for (unsigned long long m = __builtin_amdgcn_ballot_w64(I != 0); m; m &= m - 1) {
+            if (lane == __builtin_ctzll(m)) {
+                for (uint32_t b = I; b; b &= b - 1) {
+                    const int i = __builtin_ctz(b), j = lane_next(live, i), k = lane_next(live, j);
+                    Line l3[3];
+                    double r3[3];
+                    const int sl[3] = {i, j, k};
+                    for (int t = 0; t < 3; t++) {
+                        const int p = (int)(ls >> (4 * sl[t])) & 15, li = sh.li[p][lane];
+                        l3[t] = lane_line<RAD>(A, T, px, py, ri, li, sh.lc[p][lane]);
+                        r3[t] = RAD && li >= 0 ? A.rad[li] : 0.0;
+                    }
+                    if (lane_exact<RAD>(l3[0], r3[0], l3[1], r3[1], l3[2], r3[2], ri, ws) == 0) zb |= 1u << i;
+                    nexact++;
+                }
+            }
+        }
+        if (act && fin) {
+            // triangles (apex, v, next): the apex is the particle when it lies
+            // strictly inside the cell (every line has h > 0, always so for a
+            // Voronoi cell), else the cell's first live vertex
+            double o0 = 0.0, o1 = 0.0;
+            double w0x = 0.0, w0y = 0.0;  // first live vertex
+#pragma unroll
+            for (int i = V - 1; i >= 0; i--) {
+                const bool lv = (live >> i) & 1;
+                w0x = lv ? vx[i] : w0x;
+                w0y = lv ? vy[i] : w0y;
+            }
+            if (RAD) {
+                bool outside = false;
+                for (uint32_t b = live; b; b &= b - 1) {
+                    const int p = (int)(ls >> (4 * __builtin_ctz(b))) & 15;
+                    if (!(lane_line<RAD>(A, T, px, py, ri, sh.li[p][lane], sh.lc[p][lane]).h > 0.0)) outside = true;
+                }
+                if (outside) {
+                    o0 = w0x;
+                    o1 = w0y;
+                }
+            }
+            double ar = 0.0, m0 = 0.0, m1 = 0.0, per = 0.0, wx = w0x, wy = w0y;
+#pragma unroll
+            for (int i = V - 1; i >= 0; i--) {
+                if ((live >> i) & 1) {
+                    const double x = vx[i] - o0, y = vy[i] - o1, u = wx - o0, v = wy - o1;
+                    const double cr = x * v - y * u;
+                    ar += cr;
+                    m0 += cr * (x + u);
+                    m1 += cr * (y + v);
+                    const double dx = wx - vx[i], dy = wy - vy[i];
+                    per += sqrt(dx * dx + dy * dy);
+                    wx = vx[i];
+                    wy = vy[i];
+                }
+            }
+            const uint32_t pos = live & ~zb;
+            const int ne = __popc(pos);
+            if ((A.mask & (16 | 32)) && A.nbr) {
+                int rank = 0;
+                for (uint32_t b = pos; b; b &= b - 1) {
+                    const int p = (int)(ls >> (4 * lane_next(live, __builtin_ctz(b)))) & 15, li = sh.li[p][lane];
+                    A.nbr[(int64_t)id * kMaxNbr + rank] = li >= 0 ? A.part[li].id : li;
+                    A.nsh[(int64_t)id * kMaxNbr + rank] = sh.lc[p][lane];
+                    rank++;
+                }
+            }
+            if (A.vol) A.vol[id] = 0.5 * ar;
+            if (A.cen) {
+                A.cen[3 * (int64_t)id + 0] = o0 + m0 / (3.0 * ar);
+                A.cen[3 * (int64_t)id + 1] = o1 + m1 / (3.0 * ar);
+                A.cen[3 * (int64_t)id + 2] = 0.0;
+            }
+            if (A.nv) A.nv[id] = ne;
+            if (A.ne) A.ne[id] = ne;
+            if (A.nf) A.nf[id] = ne;
+            if (A.perim) A.perim[id] = per;
+            A.status[id] = (uint8_t)ST_OK;
+        } else if (act && st == ST_CAP) {
+            A.left_list[atomicAdd(A.left_count, 1)] = si;
+        } else if (act) {
+            // an empty radical cell has zero area and perimeter
+            const double z = st == ST_EMPTY ? 0.0 : __builtin_nan("");
+            if (A.vol) A.vol[id] = z;
+            if (A.cen) {
+                A.cen[3 * (int64_t)id] = A.cen[3 * (int64_t)id + 1] = z;
+                if (st == ST_EMPTY) A.cen[3 * (int64_t)id + 2] = z;
+            }
+            if (A.nv) A.nv[id] = 0;
+            if (A.ne) A.ne[id] = 0;
+            if (A.nf) A.nf[id] = 0;
+            if (A.perim) A.perim[id] = z;
+            A.status[id] = (uint8_t)st;
+        }
+        if (act && A.fo) {
+            uint4 *fo = reinterpret_cast<uint4 *>(A.fo + (int64_t)id * kFoLen);
+            fo[0] = fo[1] = make_uint4(0, 0, 0, 0);
+        }
+    }
+    const int tot[DC_N] = {wave_isum((int)ncand), wave_isum((int)ntest), wave_isum((int)ncut), wave_isum((int)ncut) * 2,
+                           wave_isum((int)nexact), wave_isum((int)nre), 0, wave_isum((int)nblk), 0, 0, wave_isum((int)nload)};
+#pragma unroll
+    for (int k = 0; k < DC_N; k++)
+        if (lane == k && tot[k]) atomicAdd(&A.diag[k], (unsigned long long)(uint32_t)tot[k]);
+}
+
 }  // namespace
 
-hipError_t launch_cells2d(const CellArgs &a, int precision, int waves, hipStream_t s)
+// The kernel with eight lanes per cell, over every cell or over those that
+// the lane kernel left.
+static hipError_t launch_cells2d_groups(const CellArgs &a, int precision, int waves, hipStream_t s)
 {
     if (a.rad) {
         if (precision == 1) k_cells2d<8, 2, 32, true, true><<<waves, 64, 0, s>>>(a, 0);
@@ -813,6 +1408,26 @@ hipError_t launch_cells2d(const CellArgs &a, int precision, int waves, hipStream
         else k_cells2d<8, 2, 32, false, false><<<waves, 64, 0, s>>>(a, 0);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_cells2d(const CellArgs &a, int precision, bool by_lane, int waves, hipStream_t s)
+{
+    if (!by_lane) return launch_cells2d_groups(a, precision, waves, s);
+    if (a.rad) {
+        if (precision == 1) k_cells2d_lane<true, true><<<waves, 64, 0, s>>>(a);
+        else k_cells2d_lane<false, true><<<waves, 64, 0, s>>>(a);
+    } else {
+        if (precision == 1) k_cells2d_lane<true, false><<<waves, 64, 0, s>>>(a);
+        else k_cells2d_lane<false, false><<<waves, 64, 0, s>>>(a);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    CellArgs b = a;
+    b.cell_list = a.left_list;
+    b.ncell_dev = a.left_count;
+    b.queue = a.left_queue;
+    b.chunk = 8;
+    return launch_cells2d_groups(b, precision, std::min(waves, 2048), s);
 }
 
 hipError_t launch_cells2d_spill(const CellArgs &a, int waves, hipStream_t s)

@@ -115,6 +115,11 @@ struct CellArgs {
     // spill queue for cells beyond the kernel's capacity
     int32_t *spill_list;
     int32_t *spill_count;
+    // 2D: cells the lane kernel leaves to the kernel with eight lanes per
+    // cell, in the same pass (their list, count and queue head)
+    int32_t *left_list;
+    int32_t *left_count;
+    int32_t *left_queue;
     unsigned long long *diag;  // VC_DIAG_LEN counters
     double *xscratch;          // per-wave workspace of the exact predicate
     int xscratch_len;          // doubles per wave
@@ -142,7 +147,8 @@ hipError_t launch_cells(const CellArgs &a, int precision, int slots, int waves, 
 hipError_t launch_cells_handoff(const CellArgs &a, int waves, hipStream_t s);
 hipError_t launch_cells_spill(const CellArgs &a, int waves, hipStream_t s);
 hipError_t launch_cells_group(const CellArgs &a, int precision, int cells_per_wave, int waves, hipStream_t s);
-hipError_t launch_cells2d(const CellArgs &a, int precision, int waves, hipStream_t s);
+// by_lane: one cell per lane (cells it leaves go through the other kernel)
+hipError_t launch_cells2d(const CellArgs &a, int precision, bool by_lane, int waves, hipStream_t s);
 hipError_t launch_cells2d_spill(const CellArgs &a, int waves, hipStream_t s);
 // queue: three zeroed counters; big: n ints of scratch (cells for the
 // general kernel)
