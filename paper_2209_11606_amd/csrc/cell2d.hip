@@ -830,6 +830,12 @@ constexpr int kLaneV = 12;
 typedef const __attribute__((address_space(4))) Tess *TessConst2;
 
 constexpr int kLaneB = 12;  // blocks a lane gathers at once
+// A gather of more particles than this leaves its cell to the other kernel,
+// whose eight lanes share them: a wave waits for its fullest lane (10^6
+// clustered particles, section 3.1, default grid: 69 ms without the limit, 36
+// with 640, 35 with 1,280; 200,000: 16.3, 5.8 and 6.2; by eight lanes alone 39
+// and 7.6).
+constexpr int kLaneLoad = 640;
 // The wave turns from particles to cuts once the lanes that wait are half as
 // many as those that go on (10^6 periodic cells, step: waiting for all lanes
 // 3.13 ms, half of the lanes 1.79, a third 1.75, a fifth 1.78).
@@ -1060,6 +1066,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
                     }
                 }
                 nblk += nb;
+                int got = 0;
                 // their particles' ranges, independent loads
 #pragma unroll 4
                 for (int k = 0; k < nb; k++) {
@@ -1067,9 +1074,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
                     const int s = A.start[blk], e = A.start[blk + 1];
                     sh.cur[k][lane] = s;
                     sh.end[k][lane] = e;
-                    nload += e - s;
+                    got += e - s;
                 }
+                nload += got;
                 gcur = gend = 0;
+                if (got > kLaneLoad) {
+                    st = ST_CAP;
+                    done = true;
+                }
             }
             // two particles ahead
 #define VC_LANE_NEXT(I, CODE, X, Y)                              \
