@@ -60,6 +60,18 @@ vc_status dalloc(T **p, size_t count)
     return VC_OK;
 }
 
+// device memory that a kernel on the current device can read as doubles
+bool is_local_doubles(const void *p)
+{
+    hipPointerAttribute_t a;
+    int dev = -1;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == dev && reinterpret_cast<uintptr_t>(p) % sizeof(double) == 0;
+}
+
 bool is_device_ptr(const void *p)
 {
     hipPointerAttribute_t a;
@@ -324,7 +336,7 @@ struct vc_result {
     unsigned long long *diag = nullptr;
     hipStream_t last_stream = nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;  // around the main cell kernel
-    hipEvent_t ev2 = nullptr;                 // after the spill passes
+    hipEvent_t ev2 = nullptr;                 // after the spill passes (recorded by the tuner's launches)
 };
 
 namespace {
@@ -363,22 +375,27 @@ void free_result(vc_result *r)
     delete r;
 }
 
-vc_status bin(vc_container *c, hipStream_t s)
+vc_status bin(vc_container *c, const double *xyz, hipStream_t s)
 {
-    HIP_TRY(launch_fill_i32(c->count, c->nb, 0, s));
-    HIP_TRY(launch_fill_i32(c->err, 1, 0, s));
-    HIP_TRY(launch_bin_count(c->xyz, c->n, c->dim, c->tess, c->ptess, c->blk, c->rank, c->count, c->err, s));
+    HIP_TRY(launch_clear2(c->count, c->nb, c->err, 1, s));
+    HIP_TRY(launch_bin_count(xyz, c->n, c->dim, c->tess, c->ptess, c->blk, c->rank, c->count, c->err, s));
     HIP_TRY(launch_scan(c->count, c->start, c->nb, c->scan_tmp, s));
-    HIP_TRY(launch_scatter(c->xyz, c->n, c->dim, c->ptess, c->blk, c->rank, c->start, c->sid, c->part, c->inv, s));
+    HIP_TRY(launch_scatter(xyz, c->n, c->dim, c->ptess, c->blk, c->rank, c->start, c->sid, c->part, c->inv, s));
     if (c->radical) HIP_TRY(launch_radii(c->rad_in, c->n, c->inv, c->rad, s));
     return VC_OK;
 }
 
 vc_status copy_in_and_bin(vc_container *c, const double *xyz, hipStream_t s)
 {
-    HIP_TRY(hipMemcpyAsync(c->xyz, xyz, (size_t)c->n * c->dim * sizeof(double),
-                           is_device_ptr(xyz) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
-    vc_status st = bin(c, s);
+    // positions on this device are binned where they are: the records hold
+    // their copy, and the call returns when the stream is done with them
+    const double *src = xyz;
+    if (!is_local_doubles(xyz)) {
+        HIP_TRY(hipMemcpyAsync(c->xyz, xyz, (size_t)c->n * c->dim * sizeof(double),
+                               is_device_ptr(xyz) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
+        src = c->xyz;
+    }
+    vc_status st = bin(c, src, s);
     if (st) return st;
     int32_t herr = 0;
     HIP_TRY(hipMemcpyAsync(&herr, c->err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -561,7 +578,8 @@ hipError_t enqueue_spill(const vc_container *c, const CellArgs &A, int cpw, hipS
 // The launch sequence of one compute (graph-capturable: fill kernels, no
 // memset; events only when `events` is set).
 vc_status enqueue_compute(vc_container *c, vc_result *r, hipStream_t s, bool events, const Launch &L,
-                          const int32_t *cell_list = nullptr, int ncell = -1, bool compact_subset = false)
+                          const int32_t *cell_list = nullptr, int ncell = -1, bool compact_subset = false,
+                          bool tuning = false)
 {
     CellArgs A = cell_args(c, r);
     A.vcap = L.vcap;
@@ -569,13 +587,12 @@ vc_status enqueue_compute(vc_container *c, vc_result *r, hipStream_t s, bool eve
         A.cell_list = cell_list;
         A.ncell = ncell;
     }
-    HIP_TRY(launch_fill_i32(c->queue, 8, 0, s));
-    HIP_TRY(launch_fill_i32((int32_t *)r->diag, VC_DIAG_LEN * 2, 0, s));
+    HIP_TRY(launch_clear2(c->queue, 8, (int32_t *)r->diag, VC_DIAG_LEN * 2, s));
     if (events) HIP_TRY(hipEventRecord(r->ev0, s));
     HIP_TRY(launch_main(A, c->dim, c->precision, L, c->max_waves, cells_by_lane(c->dim, c->n, L.vcap), s));
     if (events) HIP_TRY(hipEventRecord(r->ev1, s));
     HIP_TRY(enqueue_spill(c, A, L.cpw, s));
-    if (events) HIP_TRY(hipEventRecord(r->ev2, s));
+    if (events && tuning) HIP_TRY(hipEventRecord(r->ev2, s));
     if (r->mask & VC_WEINBERG) {
         // codes of every cell with a record, written at the scan of their lengths
         HIP_TRY(launch_nbr_offsets(r->wbl, r->n, r->wb_off, r->scan_tmp, s));
@@ -616,7 +633,7 @@ vc_status time_launch(vc_container *b, vc_result *r, hipStream_t s, const Launch
 {
     out = 1e30f;
     for (int rep = 0; rep <= reps; rep++) {
-        vc_status st = list ? enqueue_compute(b, r, s, true, L, list, nlist) : enqueue_compute(b, r, s, true, L);
+        vc_status st = enqueue_compute(b, r, s, true, L, list, nlist, false, true);
         if (st) return st;
         if (rep == 0) continue;
         float ms = 0.f;
@@ -1473,14 +1490,12 @@ vc_status vc_tessellate_noalloc(const double *xyz, int64_t n, const vc_options *
     // binning into the array (what must start at zero is cleared by kernels)
     k_put_tess<<<1, 1, 0, s>>>(T, tess);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(launch_fill_i32(count, T.G.nb, 0, s));
-    HIP_TRY(launch_fill_i32(err, 1, 0, s));
+    HIP_TRY(launch_clear2(count, T.G.nb, err, 1, s));
     HIP_TRY(launch_bin_count(xyz, n, opt->dim, tess, nullptr, blk, rank, count, err, s));
     HIP_TRY(launch_scan(count, start, T.G.nb, scan, s));
     HIP_TRY(launch_scatter(xyz, n, opt->dim, nullptr, blk, rank, start, sid, part, inv, s));
     // cells: the launch sequence of vc_compute on the array's buffers
-    HIP_TRY(launch_fill_i32(queue, 8, 0, s));
-    HIP_TRY(launch_fill_i32(reinterpret_cast<int32_t *>(diag), VC_DIAG_LEN * 2, 0, s));
+    HIP_TRY(launch_clear2(queue, 8, reinterpret_cast<int32_t *>(diag), VC_DIAG_LEN * 2, s));
     CellArgs A;
     std::memset(&A, 0, sizeof A);
     A.tess = tess;

@@ -143,6 +143,8 @@ hipError_t launch_radii(const double *rin, int64_t n, const int32_t *inv, double
 hipError_t launch_radii_check(const double *rin, int64_t n, double *rmax, int32_t *err, hipStream_t s);
 hipError_t launch_fill_u8(uint8_t *p, int64_t n, uint8_t v, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
+// n zeros to p and m to q
+hipError_t launch_clear2(int32_t *p, int64_t n, int32_t *q, int64_t m, hipStream_t s);
 hipError_t launch_cells(const CellArgs &a, int precision, int slots, int waves, hipStream_t s);
 hipError_t launch_cells_handoff(const CellArgs &a, int waves, hipStream_t s);
 hipError_t launch_cells_spill(const CellArgs &a, int waves, hipStream_t s);

@@ -1,0 +1,46 @@
+"""The prefix sums behind the block starts and the CSR offsets, at the sizes
+where their form changes: one workgroup up to 16,384 entries, tile totals
+added up by each workgroup up to 1,024 tiles of 2,048, and three phases beyond."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def v():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2209_11606_amd import vorohip
+    return vorohip
+
+
+# blocks of a 2D grid: the scan runs over their counts
+@pytest.mark.parametrize("grid", [(1, 1), (1, 1023), (128, 128), (1, 16385), (2048, 1), (1024, 2048), (1, 2097153)])
+def test_block_starts(v, grid):
+    n = 70_001
+    x = np.random.default_rng(5).random((n, 2))
+    c = v.vc_container_create(torch.from_numpy(x).to("cuda:0"),
+                              v.vc_options_init(2, [0, 0], [1, 1], [0, 0], grid=grid))
+    try:
+        # other positions, from the host and again from the device: a rebin's counts start at zero
+        for y in (1.0 - x, x):
+            v.vc_container_rebin(c, y if y is not x else torch.from_numpy(x).to("cuda:0"))
+        start, ids = v.vc_container_blocks(c, n)
+    finally:
+        v.vc_container_destroy(c)
+    k = np.minimum(np.floor(x * np.array(grid)).astype(np.int64), np.array(grid) - 1)
+    blk = k[:, 0] + grid[0] * k[:, 1]
+    want = np.concatenate([[0], np.cumsum(np.bincount(blk, minlength=grid[0] * grid[1]))])
+    assert np.array_equal(start, want)
+    assert np.array_equal(ids, np.argsort(blk, kind="stable"))
+
+
+# the neighbour offsets: one entry per cell
+@pytest.mark.parametrize("n", [1, 1025, 16_384, 16_385, 40_961])
+def test_neighbour_offsets(v, n):
+    x = torch.from_numpy(np.random.default_rng(n).random((n, 2))).to("cuda:0")
+    out = v.tessellate(x, [0, 0], [1, 1], [1, 1], v.VC_NEIGHBORS)
+    assert np.array_equal(out["nbr_off"], np.concatenate([[0], np.cumsum(out["nf"])]))
+    assert len(out["nbr_ids"]) == out["nbr_off"][-1]
