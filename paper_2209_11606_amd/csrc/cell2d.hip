@@ -827,8 +827,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 // ---------------------------------------------------------------------------
 constexpr int kLaneV = 12;
 
-typedef const __attribute__((address_space(4))) Tess *TessConst2;
-
 constexpr int kLaneB = 12;  // blocks a lane gathers at once
 // A gather of more particles than this leaves its cell to the other kernel,
 // whose eight lanes share them: a wave waits for its fullest lane (10^6
@@ -858,7 +856,7 @@ struct Line {
 // bisector of the cell's particle and the particle at (x, y) moved by the
 // image code's periods
 template <bool RAD>
-__device__ __forceinline__ void lane_bisector(const CellArgs &A, TessConst2 T, double px, double py, double ri, double x,
+__device__ __forceinline__ void lane_bisector(const CellArgs &A, TessConst T, double px, double py, double ri, double x,
                                               double y, int code, int idx, double &q0, double &q1, double &d2, double &h)
 {
     q0 = x - px;
@@ -874,7 +872,7 @@ __device__ __forceinline__ void lane_bisector(const CellArgs &A, TessConst2 T, d
 }
 
 template <bool RAD>
-__device__ __forceinline__ Line lane_line(const CellArgs &A, TessConst2 T, double px, double py, double ri, int li, int code)
+__device__ __forceinline__ Line lane_line(const CellArgs &A, TessConst T, double px, double py, double ri, int li, int code)
 {
     Line r;
     if (li >= 0) {
@@ -924,7 +922,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
     __shared__ LaneLds sh;
     const int lane = __lane_id();
     double *ws = A.xscratch + (size_t)blockIdx.x * A.xscratch_len;
-    TessConst2 T = (TessConst2)(uintptr_t)A.tess;
+    TessConst T = (TessConst)(uintptr_t)A.tess;
     const int noff = min(A.noff, 96);
     for (int k = lane; k < noff; k += 64) sh.offs[k] = (A.offs[k].dx + 8) | (A.offs[k].dy + 8) << 8 | A.offs[k].m << 16;
     lds_sync2();

@@ -6,15 +6,16 @@
 // bisectors, Eq. 1-3) and by one triangle (a, b, c) of plane ids per vertex,
 // listing the faces that meet there counter-clockwise seen from outside.
 // Each lane owns S triangle slots in registers (vertex position in FP64).
-// An LDS table etab[a][b] names the slot holding the directed edge a -> b,
-// so the triangle across any edge is one LDS read.
+// An LDS table nb holds for every edge of every triangle the number of the
+// same edge in the triangle across it, so that triangle is one LDS read.
 //
 // A cut by plane p (Eq. 3): every lane tests its vertices, s = q.v - q.q/2,
 // a ballot gives the conflict set (vertices strictly outside).  Conflict
 // triangles whose neighbour across an edge (a -> b) survives contribute the
 // boundary edge (a, b); each becomes a new triangle (a, b, p), whose vertex is
 // the intersection of planes a, b, p (Cramer's rule).  New triangles fill free
-// slots in lane order.  No cyclic walk of the new face is needed.
+// slots in slot order, and the lane that owns the slot computes the vertex.
+// No cyclic walk of the new face is needed.
 //
 // Side decisions: |s| <= tau * M (M >= sum |q_d v_d| + |h|) is decided
 // exactly from the three planes of the vertex (s * det3 = det4 of the plane
@@ -22,8 +23,9 @@
 // kept.  With exact decisions the cell does not depend on the cut order.
 //
 // Candidates come block by block from a precomputed list of block offsets in
-// nearest-first order; the particles of up to 64 blocks are loaded at once
-// and taken in increasing distance.  A candidate at distance >= 2R (R the
+// nearest-first order; the particles of up to 64 blocks are loaded 64 at a
+// time and each 64 taken in increasing distance (a batch again leaves out the
+// blocks and particles that the cuts so far have put out of reach).  A candidate at distance >= 2R (R the
 // largest vertex distance) is skipped and the sweep stops when the next block
 // is farther than 2R (the radius bound of section 2.1.3).  Past the list the
 // search runs Chebyshev shells of blocks under the block bound of the same
@@ -38,12 +40,14 @@ namespace {
 
 template <int S, int MAXP, int K>
 struct CellLDS {
-    double pq[MAXP][4];       // plane normal q (or wall normal) and offset h
+    alignas(16) double pq[MAXP][4];  // plane normal q (or wall normal) and offset h
     double prj[MAXP];         // radius of each plane's neighbour (radical planes)
     int32_t plab[MAXP];       // neighbour id, or wall label
     uint8_t psh[MAXP];        // image code
     uint8_t pwall[MAXP];      // 1: wall plane (exact offset stored)
-    uint8_t etab[MAXP][MAXP]; // slot of the triangle holding directed edge a -> b
+    // edge k of slot t is number 4 t + k: nb[it] is the number of the same
+    // edge in the triangle across it
+    alignas(8) uint16_t nb[4 * S * 64];
     union alignas(16) {
         struct {              // statistics
             double pos[S * 64][3];
@@ -51,21 +55,29 @@ struct CellLDS {
             int32_t lab[S * 64];
         } st;
         struct {              // candidate sweep: the current batch sorted by
-            double cq[64][4];               // distance (q, |q|^2), and the
-            double ch[64];                  // new vertices of a cut; plane
-            double crj[64];                 // offsets and radii
+            double cq[64][4];               // distance (q, |q|^2), plane offsets
+            double ch[64];                  // and radii
+            double crj[64];
             int32_t cid[64];
             uint8_t ccode[64];
-            double npos[S * 64 + 8][3];
         } gc;
+        float4 bbl[S * 64];                 // ball list of the block bound
     } u;
-    uint16_t bedge[S * 64 + 8];
-    int32_t cpre[64];
-    int32_t cbeg[64];
-    uint8_t csh[64];
-    int32_t forder[MAXP];
-    int32_t fref[MAXP];
-    int32_t fo[kFoLen];
+    union alignas(16) {
+        struct {
+            uint32_t key[64 + 4];           // ranking keys of a batch
+            uint8_t mark[64];               // block of each lane
+        } b;
+        struct {
+            uint32_t bedge[S * 64];         // CUT: boundary edges a | b << 8 | number << 16
+            uint16_t first[MAXP];           // 4 x slot of the new triangle whose first plane is a
+        } c;
+        struct {                            // statistics of the faces
+            int32_t forder[MAXP];
+            int32_t fref[MAXP];
+            int32_t fo[kFoLen];
+        } st;
+    } x;
 };
 
 template <int MAXP>
@@ -102,21 +114,23 @@ struct Cell {
     float fx[S], fy[S], fz[S];
     unsigned long long live[S];
     PlaneSet<MAXP> used;
-    double R2;
-    double R;
+    uint32_t hw[S];  // squared vertex norm: its high word plus one; 0 for a free slot
+    double R2, R;    // upper bounds of the largest vertex norm and its square
     double lim;   // squared search radius
     double ri;    // the particle's radius (radical tessellation), else 0
 };
 
+// Radius bound: the largest squared vertex norm, rounded up to 20 mantissa
+// bits (kept per slot), so that the wave's maximum is one 32-bit reduction.
 template <int S, int MAXP, bool F32>
-__device__ __forceinline__ void update_radius(Cell<S, MAXP, F32> &c, int lane, const CellArgs &A)
+__device__ __forceinline__ void update_radius(Cell<S, MAXP, F32> &c, const CellArgs &A)
 {
-    double m = 0.0;
+    uint32_t m = c.hw[0];
 #pragma unroll
-    for (int s = 0; s < S; s++)
-        if ((c.live[s] >> lane) & 1) m = fmax(m, c.vx[s] * c.vx[s] + c.vy[s] * c.vy[s] + c.vz[s] * c.vz[s]);
-    c.R2 = wave_max(m);
-    c.R = sqrt(c.R2);
+    for (int s = 1; s < S; s++) m = max(m, c.hw[s]);
+    m = wave_max_u32(m);
+    c.R2 = __builtin_bit_cast(double, (unsigned long long)m << 32);
+    c.R = radius_bound(m);
     c.lim = search_lim(c.R2, c.R, A, c.ri);
 }
 
@@ -161,7 +175,7 @@ __device__ __forceinline__ int free_plane(Cell<S, MAXP, F32> &c)
 // Returns ST_OK or ST_CAP.
 template <int S, int MAXP, bool F32, int K>
 __device__ __forceinline__ int consider(const CellArgs &A, CellLDS<S, MAXP, K> &sh, Cell<S, MAXP, F32> &c, double q0, double q1,
-                        double q2, double h, double rj, int32_t lab, int code, double *ws, unsigned long long *cnt,
+                        double q2, double h, double rj, int32_t lab, int code, double *ws, uint32_t *cnt,
                         int lane)
 {
     const bool rad = A.rad != nullptr;
@@ -176,11 +190,11 @@ __device__ __forceinline__ int consider(const CellArgs &A, CellLDS<S, MAXP, K> &
         unsigned long long unsr[S];
 #pragma unroll
         for (int s = 0; s < S; s++) {
-            bool lv = (c.live[s] >> lane) & 1;
+            conf[s] = inb[s] = unsr[s] = 0;
+            if (s > 0 && !c.live[s]) continue;
             float sv = fmaf(g0, c.fx[s], fmaf(g1, c.fy[s], fmaf(g2, c.fz[s], -gh)));
-            conf[s] = __ballot(lv && sv > band32);
-            unsr[s] = __ballot(lv && !(sv > band32) && !(sv < -band32));
-            inb[s] = 0;
+            conf[s] = c.live[s] & __builtin_amdgcn_fcmpf(sv, band32, 2);          // sv > band
+            unsr[s] = c.live[s] & __builtin_amdgcn_fcmpf(fabsf(sv), band32, 13);  // |sv| <= band or NaN
             uns |= unsr[s];
             ntest += __popcll(c.live[s]);
         }
@@ -188,20 +202,20 @@ __device__ __forceinline__ int consider(const CellArgs &A, CellLDS<S, MAXP, K> &
 #pragma unroll
             for (int s = 0; s < S; s++) {
                 if (!unsr[s]) continue;
-                bool u = (unsr[s] >> lane) & 1;
                 double sv = fma(q0, c.vx[s], fma(q1, c.vy[s], fma(q2, c.vz[s], -h)));
-                conf[s] |= __ballot(u && sv > band);
-                inb[s] = __ballot(u && !(sv > band) && !(sv < -band));
+                conf[s] |= unsr[s] & __builtin_amdgcn_fcmp(sv, band, 2);
+                inb[s] = unsr[s] & __builtin_amdgcn_fcmp(fabs(sv), band, 13);
                 cnt[DC_RECHECK] += __popcll(unsr[s]);
             }
         }
     } else {
 #pragma unroll
         for (int s = 0; s < S; s++) {
-            bool lv = (c.live[s] >> lane) & 1;
+            conf[s] = inb[s] = 0;
+            if (s > 0 && !c.live[s]) continue;
             double sv = fma(q0, c.vx[s], fma(q1, c.vy[s], fma(q2, c.vz[s], -h)));
-            conf[s] = __ballot(lv && sv > band);
-            inb[s] = __ballot(lv && !(sv > band) && !(sv < -band));
+            conf[s] = c.live[s] & __builtin_amdgcn_fcmp(sv, band, 2);
+            inb[s] = c.live[s] & __builtin_amdgcn_fcmp(fabs(sv), band, 13);
             ntest += __popcll(c.live[s]);
         }
     }
@@ -212,7 +226,7 @@ __device__ __forceinline__ int consider(const CellArgs &A, CellLDS<S, MAXP, K> &
     for (int s = 0; s < S; s++) {
         unsigned long long m = inb[s];
         zero[s] = 0;
-        while (m) {
+        while (__builtin_expect(m != 0, 0)) {
             int l = __builtin_ctzll(m);
             m &= m - 1;
             int sg = 0;
@@ -255,47 +269,40 @@ __device__ __forceinline__ int consider(const CellArgs &A, CellLDS<S, MAXP, K> &
         p = free_plane(c);
         if (p < 0) return ST_CAP;
     }
-    // boundary edges of the conflict region
-    uint32_t bfl = 0;
+    lane = opaque(lane);
+    // boundary edges of the conflict region (conflict triangle edges whose
+    // twin triangle is kept), listed edge by edge of each slot
+    int m = 0;
 #pragma unroll
     for (int s = 0; s < S; s++) {
-        if ((conf[s] >> lane) & 1) {
-            uint32_t t3 = c.tp[s];
+        if (!conf[s]) continue;
+        const unsigned long long w = reinterpret_cast<const unsigned long long *>(sh.nb)[s * 64 + lane];
+        const bool mine = (conf[s] >> lane) & 1;
 #pragma unroll
-            for (int k = 0; k < 3; k++) {
-                int a = (t3 >> (8 * k)) & 0xff, b = (t3 >> (8 * ((k + 1) % 3))) & 0xff;
-                int tw = sh.etab[b][a] & (S * 64 - 1);
-                unsigned long long cw = 0;
+        for (int k = 0; k < 3; k++) {
+            const int e = (int)(w >> (16 * k)) & 0xffff, tw = (e >> 2) & (S * 64 - 1);
+            unsigned long long cw = conf[0];
 #pragma unroll
-                for (int r = 0; r < S; r++)
-                    if ((tw >> 6) == r) cw = conf[r];
-                if (!((cw >> (tw & 63)) & 1)) bfl |= 1u << (s * 3 + k);
+            for (int r = 1; r < S; r++)
+                if ((tw >> 6) == r) cw = conf[r];
+            const unsigned long long B = __builtin_amdgcn_ballot_w64(mine && !((cw >> (tw & 63)) & 1));
+            const int o = m + lane_rank(B);
+            if (((B >> lane) & 1) && o < S * 64) {
+                const uint32_t t3 = c.tp[s];
+                sh.x.c.bedge[o] = ((t3 >> (8 * k)) & 0xff) | ((t3 >> (8 * ((k + 1) % 3))) & 0xff) << 8 | (uint32_t)e << 16;
             }
+            m += __popcll(B);
         }
     }
-    int nb = __popc(bfl);
-    int m;
-    int o = ballot_excl_scan<(S == 2 ? 3 : 4)>(nb, m);
     int nfree = 0;
 #pragma unroll
     for (int s = 0; s < S; s++) nfree += __popcll(~c.live[s] | conf[s]);
-    if (m > nfree || m > S * 64 + 8) return ST_CAP;
+    if (m > nfree) return ST_CAP;
     if (A.vcap > 0) {
         int keep = 0;
 #pragma unroll
         for (int s = 0; s < S; s++) keep += __popcll(c.live[s] & ~conf[s]);
         if (keep + m > A.vcap) return ST_CAP;
-    }
-#pragma unroll
-    for (int s = 0; s < S; s++) {
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            if ((bfl >> (s * 3 + k)) & 1) {
-                uint32_t t3 = c.tp[s];
-                int a = (t3 >> (8 * k)) & 0xff, b = (t3 >> (8 * ((k + 1) % 3))) & 0xff;
-                sh.bedge[o++] = (uint16_t)(a | (b << 8));
-            }
-        }
     }
     if (lane == 0) {
         sh.pq[p][0] = q0;
@@ -308,59 +315,86 @@ __device__ __forceinline__ int consider(const CellArgs &A, CellLDS<S, MAXP, K> &
         sh.pwall[p] = 0;
     }
     __syncthreads();
-    // vertices of the new triangles (a, b, p), one per lane, staged in LDS
-    for (int k = lane; k < m; k += 64) {
-        uint16_t e = sh.bedge[k];
-        double x, y, z;
-        cramer(sh.pq[e & 0xff], sh.pq[e >> 8], sh.pq[p], x, y, z);
-        sh.u.gc.npos[k][0] = x;
-        sh.u.gc.npos[k][1] = y;
-        sh.u.gc.npos[k][2] = z;
-    }
-    __syncthreads();
-    // new triangles fill the free slots in slot order
+    // free slots in slot order take the new triangles (a, b, p) by rank; the
+    // lane that takes one computes its vertex
     int before = 0;
+    bool take[S];
+    uint32_t ed[S];
 #pragma unroll
     for (int s = 0; s < S; s++) {
-        unsigned long long fr = ~c.live[s] | conf[s];
-        int rank = before + lane_rank(fr);
-        bool take = ((fr >> lane) & 1) && rank < m;
-        unsigned long long nw = __ballot(take);
-        if (take) {
-            uint16_t e = sh.bedge[rank];
-            int a = e & 0xff, b = e >> 8;
-            c.tp[s] = (uint32_t)a | ((uint32_t)b << 8) | ((uint32_t)p << 16);
-            c.vx[s] = sh.u.gc.npos[rank][0];
-            c.vy[s] = sh.u.gc.npos[rank][1];
-            c.vz[s] = sh.u.gc.npos[rank][2];
-            if (F32) {
-                c.fx[s] = (float)c.vx[s];
-                c.fy[s] = (float)c.vy[s];
-                c.fz[s] = (float)c.vz[s];
-            }
-            uint8_t t = (uint8_t)(s * 64 + lane);
-            sh.etab[a][b] = t;
-            sh.etab[b][p] = t;
-            sh.etab[p][a] = t;
-        }
-        c.live[s] = (c.live[s] & ~conf[s]) | nw;
+        const unsigned long long fr = ~c.live[s] | conf[s];
+        const int rank = before + lane_rank(fr);
+        take[s] = ((fr >> lane) & 1) && rank < m;
         before += __popcll(fr);
+        if ((conf[s] >> lane) & 1) {
+            // a freed slot holds the particle (no bisector cuts it off) until
+            // it is taken
+            c.vx[s] = c.vy[s] = c.vz[s] = 0.0;
+            if (F32) c.fx[s] = c.fy[s] = c.fz[s] = 0.0f;
+            c.hw[s] = 0;
+        }
+        if (take[s]) {
+            ed[s] = sh.x.c.bedge[rank];
+            const int a = ed[s] & 0xff, b = (ed[s] >> 8) & 0xff;
+            const double P[4] = {q0, q1, q2, h};
+            double x, y, z;
+            cramer(sh.pq[a], sh.pq[b], P, x, y, z);
+            c.tp[s] = (ed[s] & 0xffff) | ((uint32_t)p << 16);
+            c.vx[s] = x;
+            c.vy[s] = y;
+            c.vz[s] = z;
+            if (F32) {
+                c.fx[s] = (float)x;
+                c.fy[s] = (float)y;
+                c.fz[s] = (float)z;
+            }
+            c.hw[s] = norm_key(x, y, z);
+            sh.x.c.first[a] = (uint16_t)(4 * (s * 64 + lane));
+        }
+        c.live[s] = (c.live[s] & ~conf[s]) | __builtin_amdgcn_ballot_w64(take[s]);
+        if (before >= m && s + 1 < S) {
+            // every new triangle has its slot; the later slots only lose theirs
+#pragma unroll
+            for (int r = 1; r < S; r++)
+                if (r > s) {
+                    take[r] = false;
+                    if ((conf[r] >> lane) & 1) {
+                        c.vx[r] = c.vy[r] = c.vz[r] = 0.0;
+                        if (F32) c.fx[r] = c.fy[r] = c.fz[r] = 0.0f;
+                        c.hw[r] = 0;
+                    }
+                    c.live[r] &= ~conf[r];
+                }
+            break;
+        }
+    }
+    __syncthreads();
+    // edges of the new triangle: (a, b) to the kept triangle, (b, p) to the
+    // new one whose first plane is b, as that one's edge (p, b)
+#pragma unroll
+    for (int s = 0; s < S; s++) {
+        if (take[s]) {
+            const int t = 4 * (s * 64 + lane), e = (ed[s] >> 16) & (4 * S * 64 - 1);
+            const int nx = (sh.x.c.first[(ed[s] >> 8) & 0xff] & (4 * S * 64 - 4)) | 2;
+            *reinterpret_cast<uint32_t *>(sh.nb + t) = (uint32_t)e | (uint32_t)nx << 16;
+            sh.nb[nx] = (uint16_t)(t + 1);
+            sh.nb[e] = (uint16_t)t;
+        }
     }
     c.used.w[p >> 6] |= 1ull << (p & 63);
     __syncthreads();
-    update_radius(c, lane, A);
+    update_radius(c, A);
     cnt[DC_CUTS]++;
     cnt[DC_NEWV] += m;
     return radius_ok(c) ? ST_OK : ST_CAP;
 }
 
-// The cell's vertices as the ball list of the block bound, in the
-// new-vertex buffer (unused outside cuts); returns their number.
+// The cell's vertices as the ball list of the block bound; returns their
+// number.
 template <int S, int MAXP, bool F32, int K>
 __device__ __forceinline__ int bb_list(CellLDS<S, MAXP, K> &sh, const Cell<S, MAXP, F32> &c, int lane, double extra)
 {
-    static_assert(sizeof(sh.u.gc.npos) >= sizeof(float4) * S * 64, "ball list does not fit");
-    float4 *list = reinterpret_cast<float4 *>(&sh.u.gc.npos[0][0]);
+    float4 *list = sh.u.bbl;
     int n = 0;
     __syncthreads();
 #pragma unroll
@@ -404,7 +438,7 @@ __device__ __forceinline__ bool bb_block(const CellArgs &A, CellLDS<S, MAXP, K> 
     v = v && bb_block_count<3>(A.start, T, t) > 0;
     if (!__ballot(v)) return false;
     const int nv = bb_list(sh, c, lane, extra);
-    return v && bb_meets(reinterpret_cast<const float4 *>(&sh.u.gc.npos[0][0]), nv, blo, G.bs, pad, 3);
+    return v && bb_meets(sh.u.bbl, nv, blo, G.bs, pad, 3);
 }
 
 // A batch with at least bbmin candidates inside the radius bound is first
@@ -413,74 +447,74 @@ __device__ __forceinline__ bool bb_block(const CellArgs &A, CellLDS<S, MAXP, K> 
 // one pass over the vertex list instead of a side test of every vertex.
 template <int S, int MAXP, bool F32, int K>
 __device__ __forceinline__ int gather(const CellArgs &A, CellLDS<S, MAXP, K> &sh, Cell<S, MAXP, F32> &c, int si, const double *p,
-                      const int *bc, int dx, int dy, int dz, bool valid, double *ws, unsigned long long *cnt, int lane,
-                      int bbmin, double extra, double pad)
+                      const int *bc, int dx, int dy, int dz, bool valid, int reach, TessConst T, double *ws,
+                      uint32_t *cnt, int lane, int bbmin, double extra, double pad)
 {
-    const Tess &T = A.tess[A.part[si].tess];
-    const Grid &G = T.G;
-    int dd[3] = {dx, dy, dz};
+    const int dd[3] = {dx, dy, dz};
     int bb[3], sv[3];
     bool ok = valid;
     double d2b = 0.0;
 #pragma unroll
     for (int d = 0; d < 3; d++) {
-        int t = bc[d] + dd[d];
-        if (G.per[d]) {
-            int g = G.g[d];
-            int w = ((t % g) + g) % g;
-            sv[d] = (t - w) / g;
-            bb[d] = w;
-            if (sv[d] > 2 || sv[d] < -2) ok = false;
-        } else {
-            sv[d] = 0;
-            bb[d] = t;
-            if (t < 0 || t >= G.g[d]) ok = false;
+        const int g = T->G.g[d], t = bc[d] + dd[d];
+        bb[d] = t;
+        sv[d] = 0;
+        if (T->G.per[d]) {
+            if (reach <= g) {
+                // one period at most
+                sv[d] = t < 0 ? -1 : (t >= g ? 1 : 0);
+                bb[d] = t - sv[d] * g;
+            } else {
+                const int w = ((t % g) + g) % g;
+                sv[d] = (t - w) / g;
+                bb[d] = w;
+                if (sv[d] > 2 || sv[d] < -2) ok = false;
+            }
+        } else if (t < 0 || t >= g) {
+            ok = false;
         }
-        double blo = G.lo[d] + t * G.bs[d];
-        double e = fmax(0.0, fmax(blo - p[d], p[d] - (blo + G.bs[d])));
+        const double blo = T->G.lo[d] + t * T->G.bs[d];
+        const double e = fmax(0.0, fmax(blo - p[d], p[d] - (blo + T->G.bs[d])));
         d2b += e * e;
     }
     if (d2b >= c.lim) ok = false;
-    int cntb = 0, beg = 0;
+    int rem = 0, beg = 0;  // the lane's block: particles not yet taken, the next one
     if (ok) {
-        int64_t blk = T.bbase + bb[0] + (int64_t)G.g[0] * (bb[1] + (int64_t)G.g[1] * bb[2]);
+        int64_t blk = T->bbase + bb[0] + (int64_t)T->G.g[0] * (bb[1] + (int64_t)T->G.g[1] * bb[2]);
         beg = A.start[blk];
-        cntb = A.start[blk + 1] - beg;
+        rem = A.start[blk + 1] - beg;
     }
+    const int bcode = 25 * (sv[2] + 2) + 5 * (sv[1] + 2) + (sv[0] + 2);
     cnt[DC_BLOCKS] += __popcll(__ballot(ok));
-    int incl = wave_incl_scan(cntb);
-    int total = __builtin_amdgcn_readlane(incl, 63);
-    cnt[DC_LOADED] += total;
-    if (total == 0) return ST_OK;
-    __syncthreads();
-    sh.cpre[lane] = incl - cntb;
-    sh.cbeg[lane] = beg;
-    sh.csh[lane] = (uint8_t)(25 * (sv[2] + 2) + 5 * (sv[1] + 2) + (sv[0] + 2));
-    __syncthreads();
-    for (int c0 = 0; c0 < total; c0 += 64) {
-        // load one candidate per lane
-        int ci = c0 + lane;
-        unsigned long long key = ~0ull;
+    for (;;) {
+        lane = opaque(lane);
+        // one candidate per lane, block by block; the block of a lane is the
+        // last mark at or below it
+        const int incl = wave_incl_scan(rem), pre = incl - rem;
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        if (total == 0) break;
+        cnt[DC_LOADED] += min(total, 64);
+        __syncthreads();
+        sh.x.b.mark[lane] = 0;
+        __syncthreads();
+        if (rem > 0 && pre < 64) sh.x.b.mark[pre] = (uint8_t)(lane + 1);
+        __syncthreads();
+        const int bl = max(wave_max_scan(sh.x.b.mark[lane]) - 1, 0);
+        const int idx = __shfl(beg - pre, bl) + lane, code = __shfl(bcode, bl);
         double a0 = 0.0, a1 = 0.0, a2 = 0.0, d2 = 0.0, h = 0.0, rj = 0.0;
         int32_t qid = 0;
-        int code = kNoShift;
-        if (ci < total) {
-            // last block whose exclusive prefix is <= ci
-            int lo = 0, hi = 63;
-            while (lo < hi) {
-                int mid = (lo + hi + 1) >> 1;
-                if (sh.cpre[mid] <= ci) lo = mid; else hi = mid - 1;
-            }
-            int idx = sh.cbeg[lo] + (ci - sh.cpre[lo]);
-            code = sh.csh[lo];
-            int s0 = code % 5 - 2, s1 = (code / 5) % 5 - 2, s2 = code / 25 - 2;
+        bool in = lane < total;
+        if (in) {
             Particle q = A.part[idx];
             a0 = q.x - p[0];
             a1 = q.y - p[1];
             a2 = q.z - p[2];
-            if (s0) a0 = a0 + s0 * G.L[0];
-            if (s1) a1 = a1 + s1 * G.L[1];
-            if (s2) a2 = a2 + s2 * G.L[2];
+            if (code != kNoShift) {
+                const int s0 = code % 5 - 2, s1 = (code / 5) % 5 - 2, s2 = code / 25 - 2;
+                if (s0) a0 = a0 + s0 * T->G.L[0];
+                if (s1) a1 = a1 + s1 * T->G.L[1];
+                if (s2) a2 = a2 + s2 * T->G.L[2];
+            }
             d2 = a0 * a0 + a1 * a1 + a2 * a2;
             if (A.rad) {
                 // radical plane (section 2.1.1): |x|^2 - ri^2 <= |x - q|^2 - rj^2
@@ -489,28 +523,36 @@ __device__ __forceinline__ int gather(const CellArgs &A, CellLDS<S, MAXP, K> &sh
             } else {
                 h = 0.5 * d2;
             }
-            bool self = (idx == si) && code == kNoShift;
-            if (!self && d2 < c.lim) key = __double_as_longlong(d2);
+            in = d2 < c.lim && !((idx == si) && code == kNoShift);
             qid = q.id;
         }
-        if (__popcll(__ballot(key != ~0ull)) >= bbmin) {
+        // what this batch leaves of the lane's block
+        const int taken = min(max(64 - pre, 0), rem);
+        beg += taken;
+        rem -= taken;
+        unsigned long long vm = __ballot(in);
+        if (__popcll(vm) >= bbmin) {
             const int nv = bb_list(sh, c, lane, extra);
             const double q[3] = {a0, a1, a2}, zero[3] = {0.0, 0.0, 0.0};
-            if (key != ~0ull && !bb_meets(reinterpret_cast<const float4 *>(&sh.u.gc.npos[0][0]), nv, q, zero, pad, 3))
-                key = ~0ull;
+            if (in && !bb_meets(sh.u.bbl, nv, q, zero, pad, 3)) in = false;
+            vm = __ballot(in);
         }
-        // rank the batch by (distance, lane) and store it sorted
-        unsigned long long vm = __ballot(key != ~0ull);
-        int nval = __popcll(vm);
+        // rank the batch by distance and store it sorted.  Unique 32-bit keys:
+        // the high word of the distance with the low six bits replaced by the
+        // place in the batch, so candidates closer than 2^-14 relative may swap
+        const int nval = __popcll(vm);
         if (nval == 0) continue;
-        int rank = 0;
-        for (unsigned long long m = vm; m; m &= m - 1) {
-            int j = __builtin_ctzll(m);
-            unsigned long long kj = readlane_u64(key, j);
-            rank += (kj < key) || (kj == key && j < lane);
-        }
+        const int at = lane_rank(vm);
+        const uint32_t k32 = ((uint32_t)(__builtin_bit_cast(unsigned long long, d2) >> 32) & ~63u) | (uint32_t)at;
+        if (in) sh.x.b.key[at] = k32;
+        if (lane < 3) sh.x.b.key[nval + lane] = ~0u;
         __syncthreads();
-        if (key != ~0ull) {
+        int rank = 0;
+        for (int j = 0; j < nval; j += 4) {
+            const uint4 k4 = *reinterpret_cast<const uint4 *>(&sh.x.b.key[j]);
+            rank += (k4.x < k32) + (k4.y < k32) + (k4.z < k32) + (k4.w < k32);
+        }
+        if (in) {
             sh.u.gc.cq[rank][0] = a0;
             sh.u.gc.cq[rank][1] = a1;
             sh.u.gc.cq[rank][2] = a2;
@@ -523,28 +565,37 @@ __device__ __forceinline__ int gather(const CellArgs &A, CellLDS<S, MAXP, K> &sh
             sh.u.gc.ccode[rank] = (uint8_t)code;
         }
         __syncthreads();
+        // a coincident particle (it sorts first)
+        if (__ballot(in && d2 == 0.0)) {
+            cnt[DC_CAND]++;
+            return ST_DUP;
+        }
         // nearest first; stop at the first candidate beyond 2R
         for (int k = 0; k < nval; k++) {
             double md2 = sh.u.gc.cq[k][3];
-            if (!(md2 < c.lim)) break;
+            // past the sorting's resolution the rest lies beyond too (a
+            // candidate just beyond cuts nothing)
+            if (!(md2 * (1.0 - 0x1p-13) < c.lim)) break;
             cnt[DC_CAND]++;
-            if (md2 == 0.0) return ST_DUP;
             int st = consider<S, MAXP, F32, K>(A, sh, c, sh.u.gc.cq[k][0], sh.u.gc.cq[k][1], sh.u.gc.cq[k][2],
                                                A.rad ? sh.u.gc.ch[k] : 0.5 * md2, A.rad ? sh.u.gc.crj[k] : 0.0,
                                                sh.u.gc.cid[k], sh.u.gc.ccode[k], ws,
                                                cnt, lane);
             if (st != ST_OK) return st;
         }
+        // blocks that the cuts have put out of reach
+        if (d2b >= c.lim) rem = 0;
     }
     return ST_OK;
 }
 
 template <int S, int MAXP, bool F32, int K>
-__device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &sh, int si, double *ws, unsigned long long *cnt)
+__device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &sh, int si, double *ws, uint32_t *cnt)
 {
-    const int lane = __lane_id();
+    int lane = opaque(__lane_id());
     const Particle me = A.part[si];
     const Tess &T = A.tess[me.tess];
+    TessConst TC = (TessConst)(uintptr_t)(A.tess + __builtin_amdgcn_readfirstlane(me.tess));
     const Grid &G = T.G;
     const double p[3] = {me.x, me.y, me.z};
     const int id = me.id;
@@ -582,6 +633,7 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
         c.vx[s] = c.vy[s] = c.vz[s] = 0.0;
         c.fx[s] = c.fy[s] = c.fz[s] = 0.0f;
         c.live[s] = 0;
+        c.hw[s] = 0;
     }
     c.live[0] = 0xffull;
     if (lane < 8) {
@@ -602,19 +654,21 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
         c.fx[0] = (float)e[0];
         c.fy[0] = (float)e[1];
         c.fz[0] = (float)e[2];
-        uint32_t t3 = c.tp[0];
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            int a = (t3 >> (8 * k)) & 0xff, b = (t3 >> (8 * ((k + 1) % 3))) & 0xff;
-            sh.etab[a][b] = (uint8_t)lane;
-        }
+        c.hw[0] = norm_key(e[0], e[1], e[2]);
+        // the corners across the edges of planes X Y, Y Z and Z X differ in z,
+        // x and y; a corner and its neighbour list these planes in opposite
+        // senses, so a corner's edges 0, 1, 2 are its neighbours' 2, 1, 0
+        const int nz = 4 * (lane ^ 4), nx = 4 * (lane ^ 1), ny = 4 * (lane ^ 2);
+        sh.nb[4 * lane] = (uint16_t)(((neg & 1) ? ny : nz) + 2);
+        sh.nb[4 * lane + 1] = (uint16_t)(nx + 1);
+        sh.nb[4 * lane + 2] = (uint16_t)((neg & 1) ? nz : ny);
     }
 #pragma unroll
     for (int w = 0; w < PlaneSet<MAXP>::W; w++) c.used.w[w] = 0;
     c.used.w[0] = 0x3full;
     c.used.w[PlaneSet<MAXP>::W - 1] |= PlaneSet<MAXP>::pad;
     __syncthreads();
-    update_radius(c, lane, A);
+    update_radius(c, A);
 
     // the balls of the block bound: radical widening and rounding allowance
     const double extra = rad ? fmax(*A.rmax * *A.rmax - c.ri * c.ri, 0.0) : 0.0;
@@ -640,8 +694,8 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
             v = bb_block(A, sh, c, T, p, t, v, extra, pad, lane, met);
             if (!__ballot(v)) continue;
         }
-        int st = gather<S, MAXP, F32, K>(A, sh, c, si, p, bc, of.dx, of.dy, of.dz, v, ws, cnt, lane, kBbMinList, extra,
-                                         pad);
+        int st = gather<S, MAXP, F32, K>(A, sh, c, si, p, bc, of.dx, of.dy, of.dz, v, kOffRadius, TC, ws, cnt, lane,
+                                         kBbMinList, extra, pad);
         if (st != ST_OK) return st;
     }
     // beyond the list: whole Chebyshev shells, until the radius bound holds
@@ -713,9 +767,10 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
                     const int nv = bb_list(sh, c, lane, extra);
                     const double blo[3] = {G.lo[0] + (bc[0] + dx) * G.bs[0] - p[0], G.lo[1] + (bc[1] + dy) * G.bs[1] - p[1],
                                            G.lo[2] + (bc[2] + dz) * G.bs[2] - p[2]};
-                    v = v && bb_meets(reinterpret_cast<const float4 *>(&sh.u.gc.npos[0][0]), nv, blo, G.bs, pad, 3);
+                    v = v && bb_meets(sh.u.bbl, nv, blo, G.bs, pad, 3);
                     if (!__ballot(v)) continue;
-                    int st = gather<S, MAXP, F32, K>(A, sh, c, si, p, bc, dx, dy, dz, v, ws, cnt, lane, 1, extra, pad);
+                    int st = gather<S, MAXP, F32, K>(A, sh, c, si, p, bc, dx, dy, dz, v, r, TC, ws, cnt, lane, 1, extra,
+                                                     pad);
                     if (st != ST_OK) return st;
                 }
             }
@@ -724,6 +779,7 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
     }
 
     // ---- statistics (a8) ----
+    lane = opaque(lane);
     __syncthreads();
 #pragma unroll
     for (int s = 0; s < S; s++) {
@@ -736,63 +792,20 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
         sh.u.st.lab[t] = t;
     }
     for (int k = lane; k < MAXP; k += 64) {
-        sh.forder[k] = 0;
-        sh.fref[k] = 0x7fffffff;
+        sh.x.st.forder[k] = 0;
+        sh.x.st.fref[k] = 0x7fffffff;
     }
-    if (lane < kFoLen) sh.fo[lane] = 0;
+    if (lane < kFoLen) sh.x.st.fo[lane] = 0;
     __syncthreads();
     for (int t = lane; t < S * 64; t += 64) {
         uint32_t t3 = sh.u.st.tpl[t];
         if (t3 == 0xffffffffu) continue;
-        for (int k = 0; k < 3; k++) atomicMin(&sh.fref[(t3 >> (8 * k)) & 0xff], t);
+        for (int k = 0; k < 3; k++) atomicMin(&sh.x.st.fref[(t3 >> (8 * k)) & 0xff], t);
     }
     __syncthreads();
-    // Zero-length edges (a degenerate vertex split over several triangles):
-    // the edge (a, b) between slot t and its twin has zero length when the
-    // vertex of t lies on the twin's third plane d.  Bit (s*3+k) of zb.
-    uint32_t zb = 0, ib = 0;
-    for (int j = 0; j < 3 * S; j++) {
-        int t = (j / 3) * 64 + lane, k = j % 3;
-        uint32_t t3 = sh.u.st.tpl[t];
-        if (t3 == 0xffffffffu) continue;
-        int a = (t3 >> (8 * k)) & 0xff, b = (t3 >> (8 * ((k + 1) % 3))) & 0xff;
-        uint32_t w3 = sh.u.st.tpl[sh.etab[b][a] & (S * 64 - 1)];
-        int d = (int)(w3 & 0xff) + (int)((w3 >> 8) & 0xff) + (int)((w3 >> 16) & 0xff) - a - b;
-        d = min(max(d, 0), MAXP - 1);
-        const double *nd = sh.pq[d];
-        const double *v = sh.u.st.pos[t];
-        double sd = nd[0] * v[0] + nd[1] * v[1] + nd[2] * v[2] - nd[3];
-        double bd = A.tau * ((fabs(nd[0]) + fabs(nd[1]) + fabs(nd[2])) * c.R + fabs(nd[3]));
-        if (!(sd < -bd)) ib |= 1u << j;
-    }
-    if (__ballot(ib != 0)) {
-        for (int j = 0; j < 3 * S; j++) {
-            unsigned long long m = __ballot((ib >> j) & 1);
-            while (m) {
-                int l = __builtin_ctzll(m);
-                m &= m - 1;
-                if (lane == l) {
-                    int t = (j / 3) * 64 + lane, k = j % 3;
-                    uint32_t t3 = sh.u.st.tpl[t];
-                    int a = (t3 >> (8 * k)) & 0xff, b = (t3 >> (8 * ((k + 1) % 3))) & 0xff;
-                    uint32_t w3 = sh.u.st.tpl[sh.etab[b][a] & (S * 64 - 1)];
-                    int d = (int)(w3 & 0xff) + (int)((w3 >> 8) & 0xff) + (int)((w3 >> 16) & 0xff) - a - b;
-                    d = min(max(d, 0), MAXP - 1);
-                    int sg = rad ? exact_side3(plane_r(sh, t3 & 0xff, c.ri), plane_r(sh, (t3 >> 8) & 0xff, c.ri),
-                                               plane_r(sh, (t3 >> 16) & 0xff, c.ri), plane_r(sh, d, c.ri), ws)
-                                 : exact_side3(plane_of(sh, t3 & 0xff), plane_of(sh, (t3 >> 8) & 0xff),
-                                               plane_of(sh, (t3 >> 16) & 0xff), plane_of(sh, d), ws);
-                    if (sg == 0) zb |= 1u << j;
-                }
-                cnt[DC_EXACT]++;
-            }
-        }
-    }
-    // face orders and the fan over each face from its reference vertex:
-    // tetrahedra (0, r_a, v_twin, v_t), the twin across a -> b being the
-    // previous vertex of face a counter-clockwise
-    // The apex is the particle when it lies strictly inside the cell (every
-    // face offset h > 0, always so for a Voronoi cell), else one vertex.
+    // The apex of the fan is the particle when it lies strictly inside the
+    // cell (every face offset h > 0, always so for a Voronoi cell), else one
+    // vertex.
     double o0 = 0.0, o1 = 0.0, o2 = 0.0;
     if (rad) {
         bool in = true;
@@ -811,16 +824,29 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
             o2 = sh.u.st.pos[t0][2];
         }
     }
+    // One pass over the edges (a, b) of every live triangle.  Zero length: the
+    // edge between slot t and its twin has zero length when the vertex of t
+    // lies on the twin's third plane d (bit s*3+k of zb).  Face orders count
+    // the other edges; the fan over each face from its reference vertex,
+    // tetrahedra (0, r_a, v_twin, v_t), takes them all (the twin across a -> b
+    // is the previous vertex of face a counter-clockwise).
+    uint32_t zb = 0, ib = 0;
     double v6 = 0.0, m0 = 0.0, m1 = 0.0, m2 = 0.0;
     for (int j = 0; j < 3 * S; j++) {
+        if (!c.live[j / 3]) continue;
         int t = (j / 3) * 64 + lane, k = j % 3;
         uint32_t t3 = sh.u.st.tpl[t];
         if (t3 == 0xffffffffu) continue;
-        int a = (t3 >> (8 * k)) & 0xff, b = (t3 >> (8 * ((k + 1) % 3))) & 0xff;
-        if (!((zb >> j) & 1)) atomicAdd(&sh.forder[a], 1);
-        const double *r0 = sh.u.st.pos[sh.fref[a]];
-        const double *w0 = sh.u.st.pos[sh.etab[b][a] & (S * 64 - 1)];
+        const int a = (t3 >> (8 * k)) & 0xff, e = sh.nb[4 * t + k], tw = (e >> 2) & (S * 64 - 1);
+        const int d = min((int)(sh.u.st.tpl[tw] >> ((e & 3) ? 8 * (e & 3) - 8 : 16)) & 0xff, MAXP - 1);
+        const double *nd = sh.pq[d];
         const double *v0 = sh.u.st.pos[t];
+        double sd = nd[0] * v0[0] + nd[1] * v0[1] + nd[2] * v0[2] - nd[3];
+        double bd = A.tau * ((fabs(nd[0]) + fabs(nd[1]) + fabs(nd[2])) * c.R + fabs(nd[3]));
+        if (!(sd < -bd)) ib |= 1u << j;
+        else atomicAdd(&sh.x.st.forder[a], 1);
+        const double *r0 = sh.u.st.pos[sh.x.st.fref[a]];
+        const double *w0 = sh.u.st.pos[tw];
         const double r[3] = {r0[0] - o0, r0[1] - o1, r0[2] - o2};
         const double w[3] = {w0[0] - o0, w0[1] - o1, w0[2] - o2};
         const double v[3] = {v0[0] - o0, v0[1] - o1, v0[2] - o2};
@@ -831,19 +857,40 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
         m1 += det * (r[1] + w[1] + v[1]);
         m2 += det * (r[2] + w[2] + v[2]);
     }
+    if (__builtin_expect(__ballot(ib != 0) != 0, 0)) {
+        for (int j = 0; j < 3 * S; j++) {
+            unsigned long long m = __ballot((ib >> j) & 1);
+            while (m) {
+                int l = __builtin_ctzll(m);
+                m &= m - 1;
+                if (lane == l) {
+                    int t = (j / 3) * 64 + lane, k = j % 3;
+                    uint32_t t3 = sh.u.st.tpl[t];
+                    const int a = (t3 >> (8 * k)) & 0xff, e = sh.nb[4 * t + k];
+                    const int d =
+                        min((int)(sh.u.st.tpl[(e >> 2) & (S * 64 - 1)] >> ((e & 3) ? 8 * (e & 3) - 8 : 16)) & 0xff, MAXP - 1);
+                    int sg = rad ? exact_side3(plane_r(sh, t3 & 0xff, c.ri), plane_r(sh, (t3 >> 8) & 0xff, c.ri),
+                                               plane_r(sh, (t3 >> 16) & 0xff, c.ri), plane_r(sh, d, c.ri), ws)
+                                 : exact_side3(plane_of(sh, t3 & 0xff), plane_of(sh, (t3 >> 8) & 0xff),
+                                               plane_of(sh, (t3 >> 16) & 0xff), plane_of(sh, d), ws);
+                    if (sg == 0) zb |= 1u << j;
+                    else atomicAdd(&sh.x.st.forder[a], 1);
+                }
+                cnt[DC_EXACT]++;
+            }
+        }
+    }
     // vertices: triangles joined by zero-length edges are one vertex
     int nvert = 0;
 #pragma unroll
     for (int s = 0; s < S; s++) nvert += __popcll(c.live[s]);
-    if (__ballot(zb != 0)) {
+    if (__builtin_expect(__ballot(zb != 0) != 0, 0)) {
         for (int it = 0; it < 4 * S * 64; it++) {
             bool ch = false;
             for (int j = 0; j < 3 * S; j++) {
                 if (!((zb >> j) & 1)) continue;
                 int t = (j / 3) * 64 + lane, k = j % 3;
-                uint32_t t3 = sh.u.st.tpl[t];
-                int a = (t3 >> (8 * k)) & 0xff, b = (t3 >> (8 * ((k + 1) % 3))) & 0xff;
-                int o = sh.u.st.lab[sh.etab[b][a] & (S * 64 - 1)];
+                int o = sh.u.st.lab[(sh.nb[4 * t + k] >> 2) & (S * 64 - 1)];
                 if (o < sh.u.st.lab[t]) {
                     sh.u.st.lab[t] = o;
                     ch = true;
@@ -864,12 +911,12 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
     bool capfail = false, foover = false;
     for (int k0 = 0; k0 < MAXP; k0 += 64) {
         int k = k0 + lane;
-        int ord = k < MAXP ? sh.forder[k] : 0;
+        int ord = k < MAXP ? sh.x.st.forder[k] : 0;
         bool real = ord >= 3;
         unsigned long long rb = __ballot(real);
         int rank = rk + lane_rank(rb);
         if (real) {
-            if (ord < kFoLen) atomicAdd(&sh.fo[ord], 1);
+            if (ord < kFoLen) atomicAdd(&sh.x.st.fo[ord], 1);
             if ((A.mask & (16 | 32)) && A.nbr) {
                 if (rank < kMaxNbr) {
                     A.nbr[(int64_t)id * kMaxNbr + rank] = sh.plab[k];
@@ -891,7 +938,7 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
         // record's scratch (zero-length edge bits, vertex numbers, degrees)
         uint8_t *wsc = reinterpret_cast<uint8_t *>(&sh.u.st.pos[0][0]);
         const int wl = wb_record<64, S>(A.wbg + (int64_t)id * kWbStride, sumord, sh.u.st.tpl, sh.u.st.lab,
-                                              TwinByPlanes<MAXP>{sh.etab}, wsc, wsc + 64 * S, wsc + 128 * S, zb, lane, 0);
+                                              TwinNumber<uint16_t>{sh.nb}, wsc, wsc + 64 * S, wsc + 128 * S, zb, lane, 0);
         if (lane == 0) A.wbl[id] = wl;
     }
     if (lane == 0) {
@@ -906,23 +953,33 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
         if (A.ne) A.ne[id] = sumord / 2;
         if (A.nf) A.nf[id] = nface;
     }
-    if (A.fo && lane < kFoLen) A.fo[(int64_t)id * kFoLen + lane] = (uint8_t)min(sh.fo[lane], 255);
+    if (A.fo && lane < kFoLen) A.fo[(int64_t)id * kFoLen + lane] = (uint8_t)min(sh.x.st.fo[lane], 255);
     if (capfail) return ST_CAP;
     if (A.lim_out && lane == 0) A.lim_out[si] = c.lim;
     return foover ? ST_FO_OVER : ST_OK;
 }
 
-// Waves per SIMD (the register allocator is held to that budget): three for
-// the two-slot main kernel (168 registers; its LDS allows three), two for
-// the four-slot one (its LDS allows two), one for the spill kernel.  At
-// three waves the two-slot kernel spills about 50 registers and still runs
-// a fifth faster than at two.  spill_mode: 0 the
+// What bounds the main kernel is instruction issue: 10^6 uniform periodic
+// cells move 0.2 GB (0.04 ms) and take 11.3 ms, 5,900 vector instructions a
+// cell, and the vector units issue in 89% of the cycles.  Measured steps of
+// that set: 19.8 ms with the plane-pair edge table, new vertices staged
+// through LDS and lane constants kept in registers over the whole search (8,500
+// instructions, three waves a SIMD, about 50 registers spilled); 21.0 with the
+// table of edge numbers and the direct vertices alone (5,880 instructions, but
+// 225 memory instructions a cell in place of 125, reloads of spilled lane
+// constants); 13.9 once lane numbers are opaque per phase and the exact
+// decision is marked unlikely, so that the spills lie around its call; 11.6
+// with four waves.
+// Waves per SIMD (the register allocator is held to that budget): four for
+// the two-slot main kernel (128 registers; five waves, 96 registers, take
+// 13.5 ms: the spills are back in the loop), two for the four-slot one, one
+// for the spill kernel.  spill_mode: 0 the
 // main pass (a cell beyond the capacity goes to the spill list), 2 a first
 // spill pass (its cells are marked SPILLED, and a cell beyond the capacity
 // goes on to the next list), 1 the last pass (beyond its capacity a cell is
 // VC_CELL_CAPACITY)
 template <int S, int MAXP, bool F32, int K, bool RAD, bool WB>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MAXP == 48 ? (S == 2 ? 3 : 2) : 1))) void k_cells(CellArgs Ain,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MAXP == 48 ? (S == 2 ? 4 : 2) : 1))) void k_cells(CellArgs Ain,
                                                                                                      int spill_mode)
 {
     // the Voronoi instantiation carries no radical code, and one without
@@ -937,14 +994,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MAXP == 48 ?
     __shared__ CellLDS<S, MAXP, K> sh;
     const int lane = __lane_id();
     double *ws = A.xscratch + (size_t)blockIdx.x * A.xscratch_len;
-    unsigned long long cnt[DC_N];
-#pragma unroll
-    for (int k = 0; k < DC_N; k++) cnt[k] = 0;
+    // counters: one cell's in scalar registers, the wave's one per lane
+    unsigned long long total = 0;
     const int ncell = A.ncell_dev ? __builtin_amdgcn_readfirstlane(*A.ncell_dev) : A.ncell;
     for (Claim q = first_claim(A, ncell); q.cell < q.end || claim(A, q, ncell);) {
         for (; q.cell < q.end; q.cell++) {
             const int ci = q.cell;
             int si = A.cell_list ? A.cell_list[ci] : ci;
+            uint32_t cnt[DC_N];
+#pragma unroll
+            for (int k = 0; k < DC_N; k++) cnt[k] = 0;
             int st = cell_run<S, MAXP, F32, K>(A, sh, si, ws, cnt);
             const int fov = st & ST_FO_OVER;
             st &= ~ST_FO_OVER;
@@ -975,20 +1034,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MAXP == 48 ?
                 } else {
                     A.status[id] = 2;
                 }
-                if (st == ST_CAP && spill_mode == 0) cnt[DC_SPILL]++;
             }
+            if (st == ST_CAP && spill_mode == 0) cnt[DC_SPILL]++;
+            uint32_t add = 0;
+#pragma unroll
+            for (int k = 0; k < DC_N; k++) add = lane == k ? cnt[k] : add;
+            total += add;
             __syncthreads();
         }
     }
-    if (lane < DC_N) {
-        unsigned long long v = 0;
-#pragma unroll
-        for (int k = 0; k < DC_N; k++)
-            if (k == lane) v = cnt[k];
-        // counters are wave-uniform except the spill count (lane 0)
-        if (lane == DC_SPILL) v = readlane_u64(cnt[DC_SPILL], 0);
-        if (v) atomicAdd(&A.diag[lane], v);
-    }
+    if (lane < DC_N && total) atomicAdd(&A.diag[lane], total);
 }
 
 }  // namespace

@@ -60,15 +60,6 @@ __device__ __forceinline__ void lds_fence()
     __builtin_amdgcn_wave_barrier();
 }
 
-// A value the compiler cannot see through: what is computed from it stays
-// where it is used.  Without it lane constants (addresses, masks, slot
-// numbers) are kept in registers over the whole search loop, and others spill.
-__device__ __forceinline__ int opaque(int v)
-{
-    __asm__ volatile("" : "+v"(v));
-    return v;
-}
-
 // the group's bits of a wave ballot
 template <int G>
 __device__ __forceinline__ uint32_t gbal(bool p, int gb)
@@ -263,18 +254,6 @@ __device__ __forceinline__ int free_plane(uint32_t used)
 // bits (the high word of the double plus one unit, kept per slot), so the
 // group maximum is a 32-bit DPP reduction.  R and the search radius are upper
 // bounds, which is all the radius test and the error bands need.
-__device__ __forceinline__ uint32_t norm_key(double x, double y, double z)
-{
-    return (uint32_t)(__builtin_bit_cast(unsigned long long, x * x + y * y + z * z) >> 32) + 1u;
-}
-
-__device__ __forceinline__ double radius_bound(uint32_t rk)
-{
-    const double R2 = __builtin_bit_cast(double, (unsigned long long)rk << 32);
-    if (R2 > 1e-30 && R2 < 1e30) return (double)__builtin_amdgcn_sqrtf((float)R2) * (1.0 + 0x1p-18);
-    return sqrt(R2) * (1.0 + 0x1p-40);
-}
-
 template <int G, int S, bool F32>
 __device__ __forceinline__ void update_radius(SCell<S, F32> &c, const CellArgs &A, double ri)
 {
@@ -321,19 +300,6 @@ __device__ __forceinline__ void cell_fail(const CellArgs &A, SL<G, S, MAXP, RAD>
 // other half of the wave idle; with 64, 4,771 -> 4,317 VALU instructions a
 // cell and the step 10.71 -> 9.80 ms (two cells per wave).
 
-// inclusive maximum over the lanes below (values >= 0)
-__device__ __forceinline__ int wave_max_scan(int v)
-{
-    v = max(v, dpp_i32<DPP_ROW_SHR1, 0xf>(0, v));
-    v = max(v, dpp_i32<DPP_ROW_SHR2, 0xf>(0, v));
-    v = max(v, dpp_i32<DPP_ROW_SHR4, 0xf>(0, v));
-    v = max(v, dpp_i32<DPP_ROW_SHR8, 0xf>(0, v));
-    v = max(v, dpp_i32<DPP_ROW_BCAST15, 0xa>(0, v));
-    v = max(v, dpp_i32<DPP_ROW_BCAST31, 0xc>(0, v));
-    return v;
-}
-
-typedef const __attribute__((address_space(4))) Tess *TessConst;
 typedef const __attribute__((address_space(4))) Offset *OffsetConst;
 typedef const __attribute__((address_space(4))) Particle *ParticleConst;
 
@@ -1029,7 +995,7 @@ __device__ __forceinline__ void ph_stats(const CellArgs &A, SL<G, S, MAXP, RAD> 
         // the vertex positions are no longer needed: their LDS holds the
         // record's scratch (zero-length edge bits, vertex numbers, degrees)
         uint8_t *wsc = reinterpret_cast<uint8_t *>(&sh.u.st.pos[0][0]);
-        wl = wb_record<G, S>(A.wbg + (int64_t)id * kWbStride, sumord, sh.u.st.tpl, sh.u.st.lab, TwinNumber{sh.nb}, wsc,
+        wl = wb_record<G, S>(A.wbg + (int64_t)id * kWbStride, sumord, sh.u.st.tpl, sh.u.st.lab, TwinNumber<uint8_t>{sh.nb}, wsc,
                                    wsc + G * S, wsc + 2 * G * S, 0u, gl, gb);
     }
     if (gl == 0) {

@@ -538,6 +538,56 @@ __device__ __forceinline__ int wave_incl_scan(int v)
     return v;
 }
 
+// A value the compiler cannot see through: what is computed from it stays
+// where it is used.  Without it lane constants (addresses, masks, slot
+// numbers) are kept in registers over the whole search loop, and others spill.
+__device__ __forceinline__ int opaque(int v)
+{
+    __asm__ volatile("" : "+v"(v));
+    return v;
+}
+
+// inclusive maximum over the lanes below (values >= 0)
+__device__ __forceinline__ int wave_max_scan(int v)
+{
+    v = max(v, dpp_i32<DPP_ROW_SHR1, 0xf>(0, v));
+    v = max(v, dpp_i32<DPP_ROW_SHR2, 0xf>(0, v));
+    v = max(v, dpp_i32<DPP_ROW_SHR4, 0xf>(0, v));
+    v = max(v, dpp_i32<DPP_ROW_SHR8, 0xf>(0, v));
+    v = max(v, dpp_i32<DPP_ROW_BCAST15, 0xa>(0, v));
+    v = max(v, dpp_i32<DPP_ROW_BCAST31, 0xc>(0, v));
+    return v;
+}
+
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
+{
+    uint32_t m = v;
+    m = max(m, (uint32_t)dpp_i32<DPP_QUAD_1032, 0xf>((int)m, (int)m));
+    m = max(m, (uint32_t)dpp_i32<DPP_QUAD_2301, 0xf>((int)m, (int)m));
+    m = max(m, (uint32_t)dpp_i32<DPP_ROW_HALF_MIRROR, 0xf>((int)m, (int)m));
+    m = max(m, (uint32_t)dpp_i32<DPP_ROW_MIRROR, 0xf>((int)m, (int)m));
+    m = max(m, (uint32_t)dpp_i32<DPP_ROW_BCAST15, 0xa>((int)m, (int)m));
+    m = max(m, (uint32_t)dpp_i32<DPP_ROW_BCAST31, 0xc>((int)m, (int)m));
+    return (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+}
+
+// Squared norm of a vertex rounded up to 20 mantissa bits: the high word of
+// the double plus one; and the norm's upper bound from it.
+__device__ __forceinline__ uint32_t norm_key(double x, double y, double z)
+{
+    return (uint32_t)(__builtin_bit_cast(unsigned long long, x * x + y * y + z * z) >> 32) + 1u;
+}
+
+__device__ __forceinline__ double radius_bound(uint32_t rk)
+{
+    const double R2 = __builtin_bit_cast(double, (unsigned long long)rk << 32);
+    if (R2 > 1e-30 && R2 < 1e30) return (double)__builtin_amdgcn_sqrtf((float)R2) * (1.0 + 0x1p-18);
+    return sqrt(R2) * (1.0 + 0x1p-40);
+}
+
+// a wave-uniform record read through the scalar cache
+typedef const __attribute__((address_space(4))) Tess *TessConst;
+
 // exclusive prefix of small non-negative counts (< 2^BITS) by bit ballots
 template <int BITS>
 __device__ __forceinline__ int ballot_excl_scan(int v, int &total)
@@ -842,22 +892,11 @@ __device__ __forceinline__ int grp_isum(int v)
     return v;
 }
 
-// slot of the triangle across edge k (planes k, k+1) of slot s, from either
-// form of the kernels' edge tables: the slot by directed edge of planes, or
-// the number 4 slot + edge of the twin by edge number
-template <int MAXP>
-struct TwinByPlanes {
-    const uint8_t (*etab)[MAXP];
-    __device__ __forceinline__ int operator()(const uint32_t *tpl, int s, int k) const
-    {
-        const uint32_t t3 = tpl[s];
-        const int a = (t3 >> (8 * k)) & 0xff, b = (t3 >> (8 * (k == 2 ? 0 : k + 1))) & 0xff;
-        return etab[b][a];
-    }
-};
-
+// slot of the triangle across edge k (planes k, k+1) of slot s, from the
+// kernels' tables of twin edges (number 4 slot + edge)
+template <class U>
 struct TwinNumber {
-    const uint8_t *nb;
+    const U *nb;
     __device__ __forceinline__ int operator()(const uint32_t *, int s, int k) const { return nb[4 * s + k] >> 2; }
 };
 
