@@ -410,14 +410,14 @@ vc_status vc_device_fma_rate(int precision, int reps, void *stream, double *tflo
  * no hipMalloc, hipFree or other allocating routine: the block-sorted
  * particles, the binning arrays, the work-queue counters, the spill list
  * and the exact predicate's workspace live in one file-scope device array of
- * about 16.0 MiB that each GPU the library runs on holds until the process
+ * about 100 MiB that each GPU the library runs on holds until the process
  * ends.  Inputs and outputs are the caller's device memory:
  *   xyz: n x dim doubles (particle-major), 1 <= n <= 65536, inside the box
  *   of *opt (a coordinate outside it marks every cell VC_CELL_RANGE, on the
  *   device: the call does not synchronise); the grid of *opt may hold at
  *   most 65536 blocks; no radii.  Launch fields of *opt are used as by
  *   vc_container_create (waves of the forms that decide exactly in the main
- *   kernel, one cell per wavefront and 2D, capped at 512).
+ *   kernel, one cell per wavefront and 2D, capped at 4,096).
  *   vol (n), cen (3n), nv, ne (n), fo (n x VC_FO_LEN): written when non-NULL;
  *   nf (n) and status (n) are required.  Fields are indexed by input order
  *   and equal those of vc_compute with the same options.

@@ -785,7 +785,13 @@ vc_status result_create(const vc_container *c, uint32_t mask, vc_result **out)
 
 constexpr int64_t kNaMaxN = 1 << 16;       // particles per call
 constexpr int64_t kNaMaxBlocks = 1 << 16;  // blocks of the grid
-constexpr int kNaWaves = 512;              // resident cell waves (exact-predicate workspace)
+// Cell waves of the main pass that have an exact-predicate workspace: as many
+// as the one-cell kernel keeps resident on the chip.  A step of 5,003 periodic
+// particles takes 418 us with 512 (two to a compute unit), 239 with 1,024, 163
+// with 2,048 and 134 with 4,096, for 24 KiB each.  The later passes have few
+// cells.
+constexpr int kNaWaves = 4096;
+constexpr int kNaPassWaves = 512;
 constexpr int kNaXLen = 3072;              // workspace doubles per wave
 constexpr int kNaMaxDevices = 64;
 
@@ -807,7 +813,7 @@ constexpr size_t kNaErr = kNaScan + na_align(4 * 1024);
 constexpr size_t kNaQueue = kNaErr + 256;
 constexpr size_t kNaDiag = kNaQueue + 256;
 constexpr size_t kNaX = kNaDiag + na_align(8 * VC_DIAG_LEN);
-constexpr size_t kNaBytes = kNaX + (size_t)8 * kNaWaves * kNaXLen;  // about 16.0 MiB
+constexpr size_t kNaBytes = kNaX + (size_t)8 * kNaWaves * kNaXLen;  // about 100 MiB
 
 static __device__ __align__(256) unsigned char scratch[kNaBytes];
 
@@ -1543,18 +1549,18 @@ vc_status vc_tessellate_noalloc(const double *xyz, int64_t n, const vc_options *
     B.chunk = 1;
     B.vcap = 0;
     if (opt->dim == 2) {
-        HIP_TRY(launch_cells2d_spill(B, kNaWaves, s));
+        HIP_TRY(launch_cells2d_spill(B, kNaPassWaves, s));
     } else {
         if (cpw > 1) {
             CellArgs H = B;
             H.spill_list = reinterpret_cast<int32_t *>(b + kNaSpill2);
             H.spill_count = queue + 7;
-            HIP_TRY(launch_cells_handoff(H, kNaWaves, s));
+            HIP_TRY(launch_cells_handoff(H, kNaPassWaves, s));
             B.cell_list = H.spill_list;
             B.queue = queue + 6;
             B.ncell_dev = queue + 7;
         }
-        HIP_TRY(launch_cells_spill(B, kNaWaves, s));
+        HIP_TRY(launch_cells_spill(B, kNaPassWaves, s));
     }
     k_flag_range<<<(int)std::min<int64_t>((n + 255) / 256, 256), 256, 0, s>>>(err, status, n);
     HIP_TRY(hipGetLastError());
