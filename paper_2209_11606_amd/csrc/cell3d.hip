@@ -937,8 +937,12 @@ __device__ __forceinline__ int cell_run(const CellArgs &A, CellLDS<S, MAXP, K> &
         // the vertex positions are no longer needed: their LDS holds the
         // record's scratch (zero-length edge bits, vertex numbers, degrees)
         uint8_t *wsc = reinterpret_cast<uint8_t *>(&sh.u.st.pos[0][0]);
-        const int wl = wb_record<64, S>(A.wbg + (int64_t)id * kWbStride, sumord, sh.u.st.tpl, sh.u.st.lab,
-                                              TwinNumber<uint16_t>{sh.nb}, wsc, wsc + 64 * S, wsc + 128 * S, zb, lane, 0);
+        uint8_t *rec = A.wbg + (int64_t)id * kWbStride;
+        const TwinNumber<uint16_t> tw{sh.nb};
+        const int wl = __builtin_expect(__ballot(zb != 0) != 0, 0)
+                           ? wb_record<64, S>(rec, sumord, sh.u.st.tpl, sh.u.st.lab, tw, wsc, wsc + 64 * S,
+                                              wsc + 128 * S, zb, lane, 0)
+                           : wb_simple<64, S>(rec, sumord, sh.u.st.tpl, tw, wsc + 64 * S, lane, 0);
         if (lane == 0) A.wbl[id] = wl;
     }
     if (lane == 0) {

@@ -215,7 +215,6 @@ struct SL {
         struct {               // the statistics of the finished cell
             double pos[G * S][3];
             uint32_t tpl[G * S];
-            int32_t lab[G * S];
             int32_t forder[MAXP];
             int32_t fref[MAXP];
             int32_t fo[kFoLen];
@@ -878,7 +877,6 @@ __device__ __forceinline__ void ph_stats(const CellArgs &A, SL<G, S, MAXP, RAD> 
         sh.u.st.pos[t][0] = c.vx[s];
         sh.u.st.pos[t][1] = c.vy[s];
         sh.u.st.pos[t][2] = c.vz[s];
-        sh.u.st.lab[t] = t;
     }
     for (int k = gl; k < MAXP; k += G) {
         sh.u.st.forder[k] = 0;
@@ -992,11 +990,10 @@ __device__ __forceinline__ void ph_stats(const CellArgs &A, SL<G, S, MAXP, RAD> 
     }
     int wl = 0;
     if (A.wbg) {
-        // the vertex positions are no longer needed: their LDS holds the
-        // record's scratch (zero-length edge bits, vertex numbers, degrees)
-        uint8_t *wsc = reinterpret_cast<uint8_t *>(&sh.u.st.pos[0][0]);
-        wl = wb_record<G, S>(A.wbg + (int64_t)id * kWbStride, sumord, sh.u.st.tpl, sh.u.st.lab, TwinNumber<uint8_t>{sh.nb}, wsc,
-                                   wsc + G * S, wsc + 2 * G * S, 0u, gl, gb);
+        // (no edge here has zero length; the vertex positions are no longer
+        // needed, and their LDS holds the vertex numbers)
+        wl = wb_simple<G, S>(A.wbg + (int64_t)id * kWbStride, sumord, sh.u.st.tpl, TwinNumber<uint8_t>{sh.nb},
+                             reinterpret_cast<uint8_t *>(&sh.u.st.pos[0][0]), gl, gb);
     }
     if (gl == 0) {
         if (A.wbl) A.wbl[id] = wl;
@@ -1042,16 +1039,14 @@ __device__ __forceinline__ void flush_counters(const CellArgs &A, SL<G, S, MAXP,
 // spilled, and 8,032 bytes of LDS per wave (of the 8,192 that twenty waves per
 // compute unit leave); a cell that needs more than 32 plane slots goes to the
 // spill pass.  At four waves nothing is spilled and the periodic 10^6 step
-// takes 9.25 ms against 8.69.  The instantiation that writes Weinberg records
-// spills 61 registers at 96, around the record's call, and stays at four (VoroTop
-// 200,000: 4.81 ms a step against 5.00).
-template <int G, bool WB>
+// takes 9.25 ms against 8.69.
+template <int G>
 struct SyncWaves {
-    static constexpr int value = G == 32 ? (WB ? 4 : 5) : 2;
+    static constexpr int value = G == 32 ? 5 : 2;
 };
 
 template <int G, int S, int MAXP, bool F32, bool RAD, bool WB>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G, WB>::value))) void k_cells_sync(CellArgs Ain)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G>::value))) void k_cells_sync(CellArgs Ain)
 {
     // the Voronoi instantiation carries no radical code, and one without
     // Weinberg records none of their code: those pointers are compile-time

@@ -957,6 +957,56 @@ __device__ __forceinline__ int wb_walk(const uint32_t *tpl, E etab, const uint8_
     return n;
 }
 
+// The record (see wb_record) of a cell without zero-length edges: every
+// triangle is a vertex of degree three, and its neighbours are the three
+// triangles across.  vid is LDS scratch of GW * S bytes.  200,000 uniform cells
+// at two a wave: the cell kernel takes 2.33 ms with the general walks, 1.96
+// with this, 1.86 inlined at five waves a SIMD in place of four.
+template <int GW, int S, class E>
+__device__ __forceinline__ int wb_simple(uint8_t *rec, int D, const uint32_t *tpl, E etab, uint8_t *vid, int gl, int gb)
+{
+    constexpr int NT = GW * S;
+    int V = 0;
+#pragma unroll
+    for (int s = 0; s < S; s++) {
+        const int t = s * GW + gl;
+        const bool rep = tpl[t] != 0xffffffffu;
+        const unsigned long long m = grp_ballot<GW>(rep, gb);
+        if (rep) vid[t] = (uint8_t)min(V + __popcll(m & ((1ull << gl) - 1ull)), 255);
+        V += __popcll(m);
+    }
+    if (V > kWbMaxV || 3 * V != D || 3 + V + D > kWbStride) return 0;
+    wb_fence();
+    int w[S][3];
+    bool bad = false;
+#pragma unroll
+    for (int s = 0; s < S; s++) {
+        const int t = s * GW + gl;
+        if (tpl[t] == 0xffffffffu) continue;
+        const int self = vid[t];
+#pragma unroll
+        for (int k = 0; k < 3; k++) w[s][k] = vid[wb_twin<NT>(tpl, etab, t, k)];
+        bad |= w[s][0] == w[s][1] || w[s][1] == w[s][2] || w[s][2] == w[s][0] || w[s][0] == self || w[s][1] == self ||
+               w[s][2] == self;
+    }
+    if (grp_ballot<GW>(bad, gb)) return 0;
+#pragma unroll
+    for (int s = 0; s < S; s++) {
+        const int t = s * GW + gl;
+        if (tpl[t] == 0xffffffffu) continue;
+        const int v = vid[t];
+        rec[3 + v] = 3;
+#pragma unroll
+        for (int k = 0; k < 3; k++) rec[3 + V + 3 * v + k] = (uint8_t)w[s][k];
+    }
+    if (gl == 0) {
+        rec[0] = (uint8_t)V;
+        rec[1] = (uint8_t)(D & 0xff);
+        rec[2] = (uint8_t)(D >> 8);
+    }
+    return D;
+}
+
 // Write the record of a finished cell: [V][D low][D high], the degree of
 // each vertex, each vertex's neighbours in rotation order.  GW lanes hold
 // the cell, slot t = s * GW + gl; bit 3s + k of zb: edge k of the lane's
