@@ -50,12 +50,11 @@ HBM_PEAK = 8.0e12  # B/s
 # block-sorted record written (24 B of position and 4 B of id) and its block
 # count (4 B): 56 B
 BIN_BYTES_PER_PARTICLE = 56
-# what the library's rebin moves per particle: device copy of the positions
-# (24 B read + 24 B written), block count (24 B read, 8 B written),
-# provisional slot (12 B read, 4 B written), rank by id and final scatter
+# what the library's rebin moves per particle (device positions are binned
+# where they lie): block count (24 B read, 8 B written), provisional slot (12 B read, 4 B written), rank by id and final scatter
 # (24 B of position, 16 B of index, block and range, ~20 B of the block's ids
 # read; 32 B written)
-BIN_BYTES_IMPLEMENTATION = 188
+BIN_BYTES_IMPLEMENTATION = 140
 FP64_VECTOR_PEAK = 78.6e12  # FLOP/s: 256 CU x 4 SIMD x 16 lanes x 2 (FMA) x 2.4 GHz
 FLOP_WEIGHTS = dict(candidates=9, vertex_tests=6, new_vertices=12, fan_triangles=28)
 
