@@ -88,21 +88,6 @@ __device__ __forceinline__ uint32_t gmax_u32(uint32_t v)
 }
 
 template <int G>
-__device__ __forceinline__ double gmax_f64(double v)
-{
-    v = fmax(v, dpp_f64<DPP_QUAD_1032, 0xf>(v, v));
-    v = fmax(v, dpp_f64<DPP_QUAD_2301, 0xf>(v, v));
-    v = fmax(v, dpp_f64<DPP_ROW_HALF_MIRROR, 0xf>(v, v));
-    v = fmax(v, dpp_f64<DPP_ROW_MIRROR, 0xf>(v, v));
-    if (G >= 32) {
-        unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-        unsigned lo = (unsigned)swz16((int)(unsigned)u), hi = (unsigned)swz16((int)(unsigned)(u >> 32));
-        v = fmax(v, __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo));
-    }
-    return v;
-}
-
-template <int G>
 __device__ __forceinline__ int gisum(int v)
 {
     v = v + dpp_i32<DPP_QUAD_1032, 0xf>(0, v);
@@ -129,33 +114,6 @@ __device__ __forceinline__ double gsum(double v)
         v = (threadIdx.x & 16) ? w + v : v + w;
     }
     return v;
-}
-
-// inclusive prefix sum inside the group
-template <int G>
-__device__ __forceinline__ int gscan_incl(int v)
-{
-    v = v + dpp_i32<DPP_ROW_SHR1, 0xf>(0, v);
-    v = v + dpp_i32<DPP_ROW_SHR2, 0xf>(0, v);
-    v = v + dpp_i32<DPP_ROW_SHR4, 0xf>(0, v);
-    v = v + dpp_i32<DPP_ROW_SHR8, 0xf>(0, v);
-    if (G >= 32) v = v + dpp_i32<DPP_ROW_BCAST15, 0xa>(0, v);
-    return v;
-}
-
-// exclusive prefix of small counts (< 2^BITS) inside the group, by ballots
-template <int G, int BITS>
-__device__ __forceinline__ int gballot_scan(int v, int gb, uint32_t below, int &total)
-{
-    int r = 0, t = 0;
-#pragma unroll
-    for (int b = 0; b < BITS; b++) {
-        uint32_t m = gbal<G>((v >> b) & 1, gb);
-        r += __popc(m & below) << b;
-        t += __popc(m) << b;
-    }
-    total = t;
-    return r;
 }
 
 // search state of a group that only the phase steps read (kept in LDS to

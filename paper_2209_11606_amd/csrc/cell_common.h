@@ -588,21 +588,6 @@ __device__ __forceinline__ double radius_bound(uint32_t rk)
 // a wave-uniform record read through the scalar cache
 typedef const __attribute__((address_space(4))) Tess *TessConst;
 
-// exclusive prefix of small non-negative counts (< 2^BITS) by bit ballots
-template <int BITS>
-__device__ __forceinline__ int ballot_excl_scan(int v, int &total)
-{
-    int r = 0, t = 0;
-#pragma unroll
-    for (int b = 0; b < BITS; b++) {
-        unsigned long long m = __ballot((v >> b) & 1);
-        r += lane_rank(m) << b;
-        t += __popcll(m) << b;
-    }
-    total = t;
-    return r;
-}
-
 // vertex of planes A, B, C by Cramer's rule
 // vertex of lines A, B (n.r = h, rows n0 n1 h) by Cramer's rule
 __device__ __forceinline__ void cramer2(const double *A, const double *B, double &x, double &y)
