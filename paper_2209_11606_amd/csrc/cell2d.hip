@@ -1278,6 +1278,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
                 }
             }
         }
+        if (RAD && st == ST_EMPTY) {
+            // a particle that coincides with another (of the same block): a
+            // duplicate or an empty cell, by which the nearest-first order of
+            // the other kernel meets first
+            const int blk = T->bbase + bc[0] + T->G.g[0] * bc[1], end = A.start[blk + 1];
+            for (int i = A.start[blk]; i < end; i++)
+                if (i != si && A.part[i].x == px && A.part[i].y == py) st = ST_CAP;
+        }
         // ---- statistics: area, centroid, perimeter, edges, neighbours ----
         const bool fin = st == ST_OK;
         // edge from the vertex in slot i to the next: zero length when the

@@ -90,3 +90,19 @@ def test_lane_kernel_exact_and_subset(v):
             v.vc_container_destroy(c)
         for k in ("vol", "cen", "perim", "nv", "nf", "status"):
             assert np.array_equal(got[k][ids], base[k][ids]), (force, k)
+
+
+def test_lane_kernel_radical_duplicates(v):
+    """Coincident particles in a radical set, some of them with an empty cell:
+    duplicate or empty as the eight-lane kernel says, particle by particle."""
+    x = W.uniform(N, 2, 1.0, 821)
+    rad = W.rng(822).random(N) * N ** -0.5
+    idx = W.rng(823).permutation(N)
+    x[idx[:20_000]] = x[idx[20_000:40_000]]
+    a, b = run(v, x, [1, 1], rad), run(v, x, [1, 1], rad, capacity=16)
+    kinds = [v.VC_CELL_OK, v.VC_CELL_DUPLICATE, v.VC_CELL_EMPTY]
+    assert all(np.any(b["status"] == k) for k in kinds)
+    for k in kinds[1:]:
+        assert np.array_equal(a["status"] == k, b["status"] == k), k
+    for k in ("nf", "nbr_off", "nbr_ids", "nbr_sh"):
+        assert np.array_equal(a[k], b[k]), k
