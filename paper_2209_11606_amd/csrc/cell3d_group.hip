@@ -489,6 +489,13 @@ __device__ __forceinline__ int co_batch(const CellArgs &A, SL<G, S, MAXP, RAD> &
         } while (width > G && __popcll(vm) > G);
         valid = valid && lane < width;
     }
+    // radical: whether an empty cell on a coincident particle is a duplicate
+    // or empty depends on which of the two shows first, by G particles at a time
+    if (RAD && (__builtin_amdgcn_ballot_w64(valid && d2 == 0.0) & ~(unsigned long long)Gw<G>::FULL)) {
+        width = G;
+        vm &= Gw<G>::FULL;
+        valid = valid && lane < G;
+    }
     bn = __popcll(vm);
     sh.gs.gc0 = c0 + width;
     if (bn == 0) return PH_BATCH;

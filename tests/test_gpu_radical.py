@@ -203,3 +203,28 @@ def test_radical_batch(v):
         sub["nbr"] = [np.where(l[:, :1] >= 0, l - [offs[t], 0], l) for l in g["nbr"][sl]]
         ref = oracle.Oracle(m["xyz"], m["lo"], m["hi"], m["periodic"], radii=m["radii"]).cells()
         assert_radical(sub, ref, 3, v)
+
+
+@pytest.mark.parametrize("form", [dict(), dict(cells_per_wave=2), dict(cells_per_wave=4)])
+@pytest.mark.parametrize("twin,status", [(45, "VC_CELL_DUPLICATE"), (80, "VC_CELL_EMPTY")])
+def test_empty_cell_on_a_coincident_particle(v, form, twin, status):
+    """One block of 100 particles.  Particle 0 has a shell of small neighbours
+    (the particles before 32), particle 40 empties its cell, and `twin` lies on
+    it.  It is a duplicate when the twin comes among the same 16, 32 or 64
+    particles as number 40, and empty when that one comes first."""
+    r = W.rng(31)
+    x = r.random((100, 3))
+    while np.any(near := np.linalg.norm(x - 0.5, axis=1) < 0.42):
+        x[near] = r.random((near.sum(), 3))
+    k = np.arange(31) + 0.5
+    z, t = 1.0 - 2.0 * k / 31, k * math.pi * (1.0 + 5.0 ** 0.5)
+    s = np.sqrt(1.0 - z * z)
+    x[1:32] = 0.5 + 0.1 * np.stack([s * np.cos(t), s * np.sin(t), z], 1)
+    x[0] = x[twin] = 0.5
+    x[40] = [0.52, 0.5, 0.5]
+    rad = np.zeros(100)
+    rad[[0, twin]] = 0.01
+    rad[40] = 0.1
+    g = run(v, x, [0] * 3, [1] * 3, [0] * 3, rad, grid=[1, 1, 1], **form)
+    assert g["status"][0] == getattr(v, status)
+    assert g["nf"][0] == 0 and (g["vol"][0] == 0.0) == (status == "VC_CELL_EMPTY")
