@@ -410,7 +410,7 @@ vc_status vc_device_fma_rate(int precision, int reps, void *stream, double *tflo
  * no hipMalloc, hipFree or other allocating routine: the block-sorted
  * particles, the binning arrays, the work-queue counters, the spill list
  * and the exact predicate's workspace live in one file-scope device array of
- * about 100 MiB that each GPU the library runs on holds until the process
+ * about 5.5 MiB that each GPU the library runs on holds until the process
  * ends.  Inputs and outputs are the caller's device memory:
  *   xyz: n x dim doubles (particle-major), 1 <= n <= 65536, inside the box
  *   of *opt (a coordinate outside it marks every cell VC_CELL_RANGE, on the

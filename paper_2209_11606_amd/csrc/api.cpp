@@ -297,7 +297,7 @@ struct vc_container {
     int32_t *sample_list = nullptr;  // tuning sample (batches)
     int nsample = 0;
     double *xscratch = nullptr;
-    int xscratch_len = 3072;  // doubles: radical offsets make the expansions up to ~1.7x longer
+    int xscratch_len = 64 * kExactDoubles;  // doubles per wave
     int max_waves = 0;
     Launch launch;
     // graph replay (batches)
@@ -788,11 +788,11 @@ constexpr int64_t kNaMaxBlocks = 1 << 16;  // blocks of the grid
 // Cell waves of the main pass that have an exact-predicate workspace: as many
 // as the one-cell kernel keeps resident on the chip.  A step of 5,003 periodic
 // particles takes 418 us with 512 (two to a compute unit), 239 with 1,024, 163
-// with 2,048 and 134 with 4,096, for 24 KiB each.  The later passes have few
-// cells.
+// with 2,048 and 134 with 4,096.  One lane of a wave decides at a time.  The
+// later passes have few cells.
 constexpr int kNaWaves = 4096;
 constexpr int kNaPassWaves = 512;
-constexpr int kNaXLen = 3072;              // workspace doubles per wave
+constexpr int kNaXLen = kExactDoubles;     // workspace doubles per wave
 constexpr int kNaMaxDevices = 64;
 
 constexpr size_t na_align(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -813,7 +813,9 @@ constexpr size_t kNaErr = kNaScan + na_align(4 * 1024);
 constexpr size_t kNaQueue = kNaErr + 256;
 constexpr size_t kNaDiag = kNaQueue + 256;
 constexpr size_t kNaX = kNaDiag + na_align(8 * VC_DIAG_LEN);
-constexpr size_t kNaBytes = kNaX + (size_t)8 * kNaWaves * kNaXLen;  // about 100 MiB
+constexpr size_t kNaBytes = kNaX + (size_t)8 * kNaWaves * kNaXLen;
+// every program that loads the library holds it on each GPU it uses
+static_assert(kNaBytes <= (size_t)8 << 20, "the array stays small");
 
 static __device__ __align__(256) unsigned char scratch[kNaBytes];
 

@@ -104,13 +104,28 @@ __device__ inline int xs_compress(double *e, int m)
 // (every Grow-Expansion step walks the whole list, in the global workspace)
 constexpr int kXsCompressAt = 16;
 
+// The most components an accumulator holds.  Compress leaves components
+// whose exponents fall by 53 or more each, at most 40 between the largest and
+// the smallest double, and adding a product grows the list by two.  Only
+// values beyond the doubles' range (infinities and NaN, whose sign means
+// nothing) could make it longer: then the largest component stays in the last
+// place.
+constexpr int kXsLen = 48;
+
 __device__ inline int xs_add_prod(double *e, int n, double a, double b)
 {
     double x, y;
     xs_two_prod(a, b, x, y);
     if (y != 0.0) n = xs_grow(e, n, y);
     n = xs_grow(e, n, x);
-    return n > kXsCompressAt ? xs_compress(e, n) : n;
+    if (n > kXsCompressAt) {
+        n = xs_compress(e, n);
+        if (n > kXsLen - 2) {
+            e[kXsLen - 3] = e[n - 1];
+            n = kXsLen - 2;
+        }
+    }
+    return n;
 }
 
 __device__ inline int xs_sign(const double *e, int n)
@@ -387,6 +402,8 @@ __device__ __forceinline__ double radical_shift(double ri, double rj)
 {
     return ri * ri - rj * rj;
 }
+
+static_assert(kXsLen == kExactDoubles, "the workspaces hold an accumulator");
 
 #pragma clang fp contract(fast)
 

@@ -10,6 +10,7 @@ constexpr int kWave = 64;
 constexpr int kFoLen = 32;      // face-order vector length
 constexpr int kMaxNbr = 64;     // neighbour slots per cell in the fixed-stride scratch
 constexpr int kOffRadius = 4;   // Chebyshev radius of the precomputed block-offset list
+constexpr int kExactDoubles = 48; // workspace of an exact side decision
 constexpr int kNoShift = 62;    // image code of the zero shift: 25*2 + 5*2 + 2
 // Edge-graph record of one cell for the Weinberg codes: [V][D low][D high],
 // the degree of each vertex, then each vertex's neighbours in rotation
