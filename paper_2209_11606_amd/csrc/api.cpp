@@ -290,7 +290,8 @@ struct vc_container {
     Offset *offs = nullptr;
     int noff = 0;
     int32_t *queue = nullptr;    // [0]: main queue head, [1]: spill queue head, [2]: spill count,
-                                 // [3..5]: the Weinberg code kernels' heads and list count,
+                                 // [3..5]: the Weinberg code kernels' heads and list count (3D),
+                                 // 2D: [3..4]: head and count of the cells with decisions in band,
                                  // [6..7]: head and count of spill_list2
     int32_t *spill_list = nullptr;
     int32_t *spill_list2 = nullptr;  // 3D: overflows of the first spill pass; 2D: cells the lane kernel leaves
@@ -535,6 +536,8 @@ CellArgs cell_args(const vc_container *c, const vc_result *r)
     A.left_list = c->spill_list2;
     A.left_queue = c->queue + 6;
     A.left_count = c->queue + 7;
+    A.band_queue = c->queue + 3;
+    A.band_count = c->queue + 4;
     A.diag = r->diag;
     A.xscratch = c->xscratch;
     A.xscratch_len = c->xscratch_len;

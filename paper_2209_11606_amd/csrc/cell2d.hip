@@ -910,9 +910,16 @@ __device__ __forceinline__ int lane_next(uint32_t live, int i)
     return up ? i + 1 + __builtin_ctz(up) : __builtin_ctz(live);
 }
 
+// EX: the pass over the cells that the main one lists because a side decision
+// is in the exact predicate's band.  It runs them again from the start and
+// decides exactly, each lane with a workspace of its own.  With the decisions
+// in the main pass, one lane at a time, a periodic lattice of 160,000 took 2.69
+// ms a step (eight lanes a cell: 2.11), with the pass 0.80; and without the call
+// the main kernel spills nothing (100,000 particles 0.43 -> 0.41 ms, 10^6 with
+// VC_F32_FILTER 2.62 -> 2.07).
 // three waves per SIMD: at four the polygon and a cut's two lines spill (6.8
 // ms a step against 3.1 with every lane waiting), at two 3.2
-template <bool F32, bool RAD>
+template <bool F32, bool RAD, bool EX>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_cells2d_lane(CellArgs Ain)
 {
     CellArgs A = Ain;
@@ -921,14 +928,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
     constexpr uint32_t ALL = (1u << V) - 1u;
     __shared__ LaneLds sh;
     const int lane = __lane_id();
-    double *ws = A.xscratch + (size_t)blockIdx.x * A.xscratch_len;
+    double *ws = A.xscratch + (size_t)blockIdx.x * A.xscratch_len + lane * kExactDoubles;
     TessConst T = (TessConst)(uintptr_t)A.tess;
     const int noff = min(A.noff, 96);
     for (int k = lane; k < noff; k += 64) sh.offs[k] = (A.offs[k].dx + 8) | (A.offs[k].dy + 8) << 8 | A.offs[k].m << 16;
     lds_sync2();
     const double tau = A.tau;
     uint32_t ncand = 0, ntest = 0, ncut = 0, nexact = 0, nre = 0, nblk = 0, nload = 0;
-    const int ncell = A.ncell;
+    const int ncell = EX ? __builtin_amdgcn_readfirstlane(*A.ncell_dev) : A.ncell;
     for (Claim cq = first_claim(A, ncell); cq.cell < cq.end || claim(A, cq, ncell);) {
         const int ci = cq.cell + lane;
         const bool act = ci < cq.end;
@@ -999,7 +1006,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
         double R = sqrt(R2), lim = search_lim(R2, R, A, ri);
         int o = 0, n = 4;
         int st = act ? ST_OK : -1;
-        bool done = !act;
+        bool done = !act, inband = false;
         // the gathered blocks not yet opened, the open one's particles, and two
         // particles loaded ahead (index -1: none)
         int nb = 0, bi = 0, gcur = 0, gend = 0, gcode = kNoShift;
@@ -1167,23 +1174,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
                     nre += __popc(U & live);
                 }
             }
-            // in-band vertices: exact decisions, one lane at a time
-            for (unsigned long long m = __builtin_amdgcn_ballot_w64(I != 0); m; m &= m - 1) {
-                if (lane == __builtin_ctzll(m)) {
-                    const Line lp = {q0, q1, h, 0};
-                    const double rp = RAD ? A.rad[qi] : 0.0;
-                    for (uint32_t b = I; b; b &= b - 1) {
-                        const int i = __builtin_ctz(b), j = lane_next(live, i);
-                        const int pa = (int)(ls >> (4 * i)) & 15, pb = (int)(ls >> (4 * j)) & 15;
-                        const int la = sh.li[pa][lane], lb = sh.li[pb][lane];
-                        const Line a = lane_line<RAD>(A, T, px, py, ri, la, sh.lc[pa][lane]);
-                        const Line c = lane_line<RAD>(A, T, px, py, ri, lb, sh.lc[pb][lane]);
-                        const int sg = lane_exact<RAD>(a, RAD && la >= 0 ? A.rad[la] : 0.0, c,
-                                                       RAD && lb >= 0 ? A.rad[lb] : 0.0, lp, rp, ri, ws);
-                        if (sg > 0) C |= 1u << i;
-                        if (sg == 0) Z |= 1u << i;
-                        nexact++;
-                    }
+            if (!EX && I) {
+                inband = done = true;
+                C = 0;
+            }
+            if (EX && I) {
+                const Line lp = {q0, q1, h, 0};
+                const double rp = RAD ? A.rad[qi] : 0.0;
+                for (uint32_t b = I; b; b &= b - 1) {
+                    const int i = __builtin_ctz(b), j = lane_next(live, i);
+                    const int pa = (int)(ls >> (4 * i)) & 15, pb = (int)(ls >> (4 * j)) & 15;
+                    const int la = sh.li[pa][lane], lb = sh.li[pb][lane];
+                    const Line a = lane_line<RAD>(A, T, px, py, ri, la, sh.lc[pa][lane]);
+                    const Line c = lane_line<RAD>(A, T, px, py, ri, lb, sh.lc[pb][lane]);
+                    const int sg = lane_exact<RAD>(a, RAD && la >= 0 ? A.rad[la] : 0.0, c,
+                                                   RAD && lb >= 0 ? A.rad[lb] : 0.0, lp, rp, ri, ws);
+                    if (sg > 0) C |= 1u << i;
+                    if (sg == 0) Z |= 1u << i;
+                    nexact++;
                 }
             }
             if (RAD && C && !(live & ~C & ~Z)) {
@@ -1287,7 +1295,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
                 if (i != si && A.part[i].x == px && A.part[i].y == py) st = ST_CAP;
         }
         // ---- statistics: area, centroid, perimeter, edges, neighbours ----
-        const bool fin = st == ST_OK;
+        const bool fin = st == ST_OK && !inband;
         // edge from the vertex in slot i to the next: zero length when the
         // vertex lies on the line that edge's end leaves by
         uint32_t I = 0, zb = 0;
@@ -1307,24 +1315,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
                 if (!(sd < -bd)) I |= 1u << i;
             }
         }
-        for (unsigned long long m = __builtin_amdgcn_ballot_w64(I != 0); m; m &= m - 1) {
-            if (lane == __builtin_ctzll(m)) {
-                for (uint32_t b = I; b; b &= b - 1) {
-                    const int i = __builtin_ctz(b), j = lane_next(live, i), k = lane_next(live, j);
-                    Line l3[3];
-                    double r3[3];
-                    const int sl[3] = {i, j, k};
-                    for (int t = 0; t < 3; t++) {
-                        const int p = (int)(ls >> (4 * sl[t])) & 15, li = sh.li[p][lane];
-                        l3[t] = lane_line<RAD>(A, T, px, py, ri, li, sh.lc[p][lane]);
-                        r3[t] = RAD && li >= 0 ? A.rad[li] : 0.0;
-                    }
-                    if (lane_exact<RAD>(l3[0], r3[0], l3[1], r3[1], l3[2], r3[2], ri, ws) == 0) zb |= 1u << i;
-                    nexact++;
+        if (!EX && I) inband = true;
+        if (EX) {
+            for (uint32_t b = I; b; b &= b - 1) {
+                const int i = __builtin_ctz(b), j = lane_next(live, i), k = lane_next(live, j);
+                Line l3[3];
+                double r3[3];
+                const int sl[3] = {i, j, k};
+                for (int t = 0; t < 3; t++) {
+                    const int p = (int)(ls >> (4 * sl[t])) & 15, li = sh.li[p][lane];
+                    l3[t] = lane_line<RAD>(A, T, px, py, ri, li, sh.lc[p][lane]);
+                    r3[t] = RAD && li >= 0 ? A.rad[li] : 0.0;
                 }
+                if (lane_exact<RAD>(l3[0], r3[0], l3[1], r3[1], l3[2], r3[2], ri, ws) == 0) zb |= 1u << i;
+                nexact++;
             }
         }
-        if (act && fin) {
+        if (act && fin && !inband) {
             // triangles (apex, v, next): the apex is the particle when it lies
             // strictly inside the cell (every line has h > 0, always so for a
             // Voronoi cell), else the cell's first live vertex
@@ -1384,6 +1391,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
             if (A.nf) A.nf[id] = ne;
             if (A.perim) A.perim[id] = per;
             A.status[id] = (uint8_t)ST_OK;
+        } else if (act && inband) {
+            A.spill_list[atomicAdd(A.band_count, 1)] = si;
         } else if (act && st == ST_CAP) {
             A.left_list[atomicAdd(A.left_count, 1)] = si;
         } else if (act) {
@@ -1431,12 +1440,21 @@ static hipError_t launch_cells2d_groups(const CellArgs &a, int precision, int wa
 hipError_t launch_cells2d(const CellArgs &a, int precision, bool by_lane, int waves, hipStream_t s)
 {
     if (!by_lane) return launch_cells2d_groups(a, precision, waves, s);
+    // the cells with a decision in band: listed where the pass after the next
+    // lists its own, which starts when these are done
+    CellArgs x = a;
+    x.cell_list = a.spill_list;
+    x.ncell_dev = a.band_count;
+    x.queue = a.band_queue;
+    x.chunk = 64;
     if (a.rad) {
-        if (precision == 1) k_cells2d_lane<true, true><<<waves, 64, 0, s>>>(a);
-        else k_cells2d_lane<false, true><<<waves, 64, 0, s>>>(a);
+        if (precision == 1) k_cells2d_lane<true, true, false><<<waves, 64, 0, s>>>(a);
+        else k_cells2d_lane<false, true, false><<<waves, 64, 0, s>>>(a);
+        k_cells2d_lane<false, true, true><<<waves, 64, 0, s>>>(x);
     } else {
-        if (precision == 1) k_cells2d_lane<true, false><<<waves, 64, 0, s>>>(a);
-        else k_cells2d_lane<false, false><<<waves, 64, 0, s>>>(a);
+        if (precision == 1) k_cells2d_lane<true, false, false><<<waves, 64, 0, s>>>(a);
+        else k_cells2d_lane<false, false, false><<<waves, 64, 0, s>>>(a);
+        k_cells2d_lane<false, false, true><<<waves, 64, 0, s>>>(x);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

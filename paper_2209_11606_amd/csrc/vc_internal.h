@@ -121,6 +121,10 @@ struct CellArgs {
     int32_t *left_list;
     int32_t *left_count;
     int32_t *left_queue;
+    // 2D: cells the lane kernel lists (in spill_list, which is empty until the
+    // next kernel) for its pass with exact decisions
+    int32_t *band_count;
+    int32_t *band_queue;
     unsigned long long *diag;  // VC_DIAG_LEN counters
     double *xscratch;          // per-wave workspace of the exact predicate
     int xscratch_len;          // doubles per wave
