@@ -223,13 +223,16 @@ struct Launch {
 // one for each group.  Beyond that every group has a cell, and a wave makes at
 // least four grabs of at most two cells for each group: longer ones leave
 // tails (10^6 periodic cells at two per wave: grabs of two to eight cells
-// within 1%, 16 +2%, 32 +6%).  The 2D lane kernel always fills its 64 lanes
+// within 1%, 16 +2%, 32 +6%).  In 2D a grab is one or two cells for every group,
+// since its groups take them in turn (79,999 cells: 0.44 ms a step with grabs of
+// eight, 0.53 with nine).  The 2D lane kernel always fills its 64 lanes
 // (100,000 cells: 0.53 ms a step against 0.70 with 24 lanes in use).
 void fit_launch(int64_t ncell, int dim, int per_wave, int &waves, int &chunk)
 {
     if (chunk <= 0) {
         const int64_t low = dim == 2 || ncell > waves ? per_wave : 1, high = per_wave == 64 ? 64 : 2 * per_wave;
         chunk = (int)std::max(low, std::min<int64_t>(high, ncell / ((int64_t)waves * 4)));
+        if (dim == 2) chunk -= chunk % per_wave;
     } else {
         chunk = (int)std::min<int64_t>((int64_t)chunk * per_wave, INT32_MAX / 2);
     }
@@ -247,6 +250,19 @@ void fit_launch(int64_t ncell, int dim, int per_wave, int &waves, int &chunk)
 constexpr int64_t kLaneCells = 80000;
 
 bool cells_by_lane(int dim, int64_t n, int vcap) { return dim == 2 && vcap == 0 && n >= kLaneCells; }
+
+// Waves of the main pass when they are left to the library.  In 2D as many as
+// are resident: a wave's first range is fixed by its number, and one that has to
+// wait for a place starts it late (eight lanes a cell, 40,000 cells: 0.41 ms a
+// step with sixteen a compute unit, 0.32 with eight; 60,000 0.47 and 0.38; by
+// lane, 400,000 0.88 with sixteen, 0.85 with twelve).  Twenty waves of the
+// two-cell 3D form are resident; the four-cell and four-slot forms, at eight,
+// gain nothing from fewer (300,001 cells at four per wave 4.3 ms with sixteen,
+// 5.0 with eight; with four slots the same).
+int auto_waves(int dim, int cpw, bool by_lane)
+{
+    return device_cu_count() * (dim == 2 ? (by_lane ? 12 : 8) : (cpw == 2 ? 20 : 16));
+}
 
 hipError_t launch_main(CellArgs A, int dim, int precision, const Launch &L, int max_waves, bool by_lane, hipStream_t s)
 {
@@ -444,10 +460,9 @@ vc_status create_common(vc_container *c, const double *xyz, const int64_t *offse
     c->launch.chunk = opts[0].chunk;
     c->launch.cpw = opts[0].cells_per_wave > 0 ? opts[0].cells_per_wave : 1;
     c->launch.vcap = opts[0].capacity;
-    int cu = device_cu_count();
-    // twenty waves of the two-cell form are resident on a compute unit
-    c->launch.waves = opts[0].waves > 0 ? opts[0].waves : cu * (c->launch.cpw == 2 && dim == 3 ? 20 : 16);
-    c->max_waves = std::max(c->launch.waves, cu * 32);
+    c->launch.waves =
+        opts[0].waves > 0 ? opts[0].waves : auto_waves(dim, c->launch.cpw, cells_by_lane(dim, c->n, c->launch.vcap));
+    c->max_waves = std::max(c->launch.waves, device_cu_count() * 32);
     c->htess.resize((size_t)ntess);
     int64_t nb = 0;
     for (int64_t t = 0; t < ntess; t++) {
@@ -1538,12 +1553,12 @@ vc_status vc_tessellate_noalloc(const double *xyz, int64_t n, const vc_options *
     A.xscratch_len = kNaXLen;
     Launch L;
     L.slots = opt->slots > 0 ? opt->slots : 2;
-    L.waves = opt->waves > 0 ? opt->waves : kNaWaves;
+    L.waves = opt->waves;
     L.chunk = opt->chunk;
     const int cpw = L.cpw = opt->cells_per_wave > 0 ? opt->cells_per_wave : 1;
     // (the grouped kernel takes no exact-predicate workspace)
     const bool grouped = opt->dim == 3 && cpw > 1;
-    if (grouped && opt->waves <= 0) L.waves = device_cu_count() * (cpw == 2 ? 20 : 16);
+    if (opt->waves <= 0) L.waves = auto_waves(opt->dim, cpw, false);
     HIP_TRY(launch_main(A, opt->dim, opt->precision, L, grouped ? L.waves : kNaWaves,
                         cells_by_lane(opt->dim, n, opt->capacity), s));
     // the passes after the main one, as for a container
