@@ -161,7 +161,10 @@ typedef struct {
     int precision;       /* VC_FP64 or VC_F32_FILTER */
     int slots;           /* triangles per lane in the main cell kernel (2 or 4); 0: auto */
     int waves;           /* resident cell waves launched; 0: auto */
-    int chunk;           /* cells taken per work-queue grab; 0: auto (by the number of cells) */
+    int chunk;           /* cells that a group of lanes takes per work-queue grab: the groups that
+                            share a wave grab together, that many for each (1, 2 or 4 groups in
+                            3D, by cells_per_wave; 8 in 2D; a 2D wave with one cell per lane
+                            takes whole sets of 64); 0: auto (by the number of cells) */
     int cells_per_wave;  /* cells sharing one wavefront: 1, 2 or 4; 0: 1 */
     double clip;         /* > 0: every cell starts as the cube (square) of this side
                             centred on its particle, cut to the box (section 3.1.3:
@@ -362,7 +365,7 @@ vc_status vc_batch_compute(vc_batch *b, vc_result *r, int graph, void *stream);
 typedef struct {
     int slots;          /* triangles per lane: 2 or 4 (cell capacity 128 or 256 vertices) */
     int waves;          /* resident waves launched */
-    int chunk;          /* cells per work-queue grab */
+    int chunk;          /* cells that a group of lanes takes per grab, as vc_options.chunk */
     int cells_per_wave; /* cells processed together by one wave */
     float ms;           /* kernel time of the winner on the tuning sample */
     int capacity;       /* vertex capacity before the spill pass (vc_options.capacity;

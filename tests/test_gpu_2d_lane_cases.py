@@ -110,3 +110,16 @@ def test_dense_blocks_are_left(v):
         a, b = run(v, x, [1, 1], per), run(v, x, [1, 1], per, capacity=16)
         same(a, b)
         assert 1.0 < a["diag"]["cuts"] / b["diag"]["cuts"]
+
+
+@pytest.mark.parametrize("opt", [dict(chunk=1), dict(chunk=4), dict(chunk=64), dict(chunk=65), dict(chunk=2**31 - 1),
+                                 dict(waves=5), dict(waves=5, chunk=100)])
+def test_chunk_and_waves_by_lane(v, opt):
+    """Grabs and waves set by hand never change a cell."""
+    n = 80_001
+    x = W.uniform(n, 2, 1.0, 71)
+    ref, got = run(v, x, [1, 1], [1, 1]), run(v, x, [1, 1], [1, 1], **opt)
+    for k in ref:
+        if k != "diag":
+            assert np.array_equal(got[k], ref[k]), k
+    assert got["diag"] == ref["diag"]
