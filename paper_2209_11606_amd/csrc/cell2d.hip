@@ -934,12 +934,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
     for (int k = lane; k < noff; k += 64) sh.offs[k] = (A.offs[k].dx + 8) | (A.offs[k].dy + 8) << 8 | A.offs[k].m << 16;
     lds_sync2();
     const double tau = A.tau;
-    uint32_t ncand = 0, ntest = 0, ncut = 0, nexact = 0, nre = 0, nblk = 0, nload = 0;
+    // counters: the wave's one per lane
+    unsigned long long total = 0;
     const int ncell = EX ? __builtin_amdgcn_readfirstlane(*A.ncell_dev) : A.ncell;
     for (Claim cq = first_claim(A, ncell); cq.cell < cq.end || claim(A, cq, ncell);) {
         const int ci = cq.cell + lane;
         const bool act = ci < cq.end;
         cq.cell = min(cq.cell + 64, cq.end);
+        int ncand = 0, ntest = 0, ncut = 0, nexact = 0, nre = 0, nblk = 0, nload = 0;  // of the lane's cell
         int si = 0, id = 0;
         double px = 0.0, py = 0.0, ri = 0.0;
         if (act) {
@@ -1413,12 +1415,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
             uint4 *fo = reinterpret_cast<uint4 *>(A.fo + (int64_t)id * kFoLen);
             fo[0] = fo[1] = make_uint4(0, 0, 0, 0);
         }
-    }
-    const int tot[DC_N] = {wave_isum((int)ncand), wave_isum((int)ntest), wave_isum((int)ncut), wave_isum((int)ncut) * 2,
-                           wave_isum((int)nexact), wave_isum((int)nre), 0, wave_isum((int)nblk), 0, 0, wave_isum((int)nload)};
+        const int cuts = wave_isum(ncut);
+        const int tot[DC_N] = {wave_isum(ncand), wave_isum(ntest), cuts, 2 * cuts, wave_isum(nexact), wave_isum(nre),
+                               0, wave_isum(nblk), 0, 0, wave_isum(nload)};
+        int add = 0;
 #pragma unroll
-    for (int k = 0; k < DC_N; k++)
-        if (lane == k && tot[k]) atomicAdd(&A.diag[k], (unsigned long long)(uint32_t)tot[k]);
+        for (int k = 0; k < DC_N; k++) add = lane == k ? tot[k] : add;
+        total += (unsigned long long)add;
+    }
+    if (lane < DC_N && total) atomicAdd(&A.diag[lane], total);
 }
 
 }  // namespace
