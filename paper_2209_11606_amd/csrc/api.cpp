@@ -510,7 +510,7 @@ vc_status create_common(vc_container *c, const double *xyz, const int64_t *offse
     TRY(dalloc(&c->offs, offs.size()));
     TRY(dalloc(&c->queue, 8));
     TRY(dalloc(&c->spill_list, (size_t)c->n));
-    TRY(dalloc(&c->spill_list2, (size_t)c->n));
+    if (dim == 3 || cells_by_lane(dim, c->n, c->launch.vcap)) TRY(dalloc(&c->spill_list2, (size_t)c->n));
     TRY(dalloc(&c->xscratch, (size_t)c->max_waves * c->xscratch_len));
 #undef TRY
     HIP_TRY(hipMemcpyAsync(c->tess, c->htess.data(), c->htess.size() * sizeof(Tess), hipMemcpyHostToDevice, s));
@@ -1550,9 +1550,6 @@ vc_status vc_tessellate_noalloc(const double *xyz, int64_t n, const vc_options *
     A.status = status;
     A.spill_list = spill;
     A.spill_count = queue + 2;
-    A.left_list = reinterpret_cast<int32_t *>(b + kNaSpill2);
-    A.left_queue = queue + 6;
-    A.left_count = queue + 7;
     A.diag = diag;
     A.xscratch = xs;
     A.xscratch_len = kNaXLen;
@@ -1564,8 +1561,8 @@ vc_status vc_tessellate_noalloc(const double *xyz, int64_t n, const vc_options *
     // (the grouped kernel takes no exact-predicate workspace)
     const bool grouped = opt->dim == 3 && cpw > 1;
     if (opt->waves <= 0) L.waves = auto_waves(opt->dim, cpw, false);
-    HIP_TRY(launch_main(A, opt->dim, opt->precision, L, grouped ? L.waves : kNaWaves,
-                        cells_by_lane(opt->dim, n, opt->capacity), s));
+    static_assert(kNaMaxN < kLaneCells, "no planar set of this size goes by lane");
+    HIP_TRY(launch_main(A, opt->dim, opt->precision, L, grouped ? L.waves : kNaWaves, false, s));
     // the passes after the main one, as for a container
     CellArgs B = A;
     B.cell_list = spill;

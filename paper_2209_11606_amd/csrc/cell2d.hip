@@ -1280,7 +1280,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
                     bool fin = R2 < 1e300 && ax == ax && ay == ay && bx == bx && by == by;
                     R = sqrt(R2);
                     lim = search_lim(R2, R, A, ri);
-                    if (A.vcap > 0 && n > A.vcap) fin = false;
                     if (!fin) {
                         st = ST_CAP;
                         done = true;
