@@ -654,9 +654,12 @@ __device__ __forceinline__ void ph_test(const CellArgs &A, SL<G, S, MAXP, RAD> &
 }
 
 // vertex of planes A, B, C by Cramer's rule, with the reciprocal of the
-// determinant by two Newton steps (to an ulp, like a division, where the
-// determinant is a normal number with a normal reciprocal; elsewhere the
-// vertex is not finite and the cell goes to the one-cell kernel)
+// determinant by two Newton steps: what the division gives wherever it was
+// compared (volumes and centroids bit for bit those of `cramer` in 2.8 million
+// cells of uniform, crystal, radical and mixed sets; boxes of sides 2^-250 to
+// 2^256 scale exactly).  With the division the same sets take 0.3% to 0.9%
+// longer.  Where the determinant or its reciprocal is not a normal number the
+// vertex is not finite and the cell goes to the one-cell kernel.
 __device__ __forceinline__ void cut_vertex(const double *A, const double *B, const double *C, double &x, double &y,
                                            double &z)
 {
@@ -1001,7 +1004,7 @@ __device__ __forceinline__ void flush_counters(const CellArgs &A, SL<G, S, MAXP,
 
 // Occupancy target in waves per SIMD, to which the register allocator is
 // held.  The two-cells-per-wave form runs five waves: 96 registers, with 18
-// spilled, and 8,032 bytes of LDS per wave (of the 8,192 that twenty waves per
+// spilled, and 7,968 bytes of LDS per wave (of the 8,192 that twenty waves per
 // compute unit leave); a cell that needs more than 32 plane slots goes to the
 // spill pass.  At four waves nothing is spilled and the periodic 10^6 step
 // takes 9.25 ms against 8.69.
@@ -1022,9 +1025,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SyncWaves<G>
         A.wbg = nullptr;
         A.wbl = nullptr;
     }
-    static_assert(((G * S) & (G * S - 1)) == 0 && G * S <= 256, "slot count must be a power of two");
+    static_assert(((G * S) & (G * S - 1)) == 0, "slot count must be a power of two");
+    static_assert(G * S <= 64, "edge numbers are bytes, and a cut's kept slots one 64-bit mask");
     static_assert(G == 16 || G == 32, "group width");
     __shared__ SL<G, S, MAXP, RAD> shv[Gw<G>::CPW];
+    static_assert(G != 32 || sizeof(shv) <= 160 * 1024 / 20, "twenty waves a compute unit");
     const int lane = __lane_id();
     const int gl = lane % G, gb = lane - gl;
     SL<G, S, MAXP, RAD> &sh = shv[lane / G];
