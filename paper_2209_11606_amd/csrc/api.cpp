@@ -290,12 +290,12 @@ struct vc_container {
     Tess *tess = nullptr;
     int32_t *ptess = nullptr;    // tessellation of each input particle (batches only)
     int64_t nb = 0;              // blocks over all tessellations
-    double *xyz = nullptr;       // device copy of the input positions (n x dim)
+    double *xyz = nullptr;       // device copy of positions given elsewhere (n x dim)
     Particle *part = nullptr;    // block-sorted particles
     int32_t *start = nullptr;    // nb + 1
     int32_t *count = nullptr;    // nb
     int32_t *blk = nullptr;      // n
-    int32_t *rank = nullptr;     // n
+    int32_t *rank = nullptr;     // n; between binnings 2D: cells the lane kernel leaves
     int32_t *sid = nullptr;      // n: input index at each provisional slot
     int32_t *inv = nullptr;      // n: sorted slot of each input index
     int32_t *subset = nullptr;   // n: sorted slots of a subset (vc_compute_subset), on first use
@@ -313,9 +313,9 @@ struct vc_container {
     int32_t *queue = nullptr;    // [0]: main queue head, [1]: spill queue head, [2]: spill count,
                                  // [3..5]: the Weinberg code kernels' heads and list count (3D),
                                  // 2D: [3..4]: head and count of the cells with decisions in band,
-                                 // [6..7]: head and count of spill_list2
+                                 // [6..7]: head and count of spill_list2 (3D) or of the cells left (2D)
     int32_t *spill_list = nullptr;
-    int32_t *spill_list2 = nullptr;  // 3D: overflows of the first spill pass; 2D: cells the lane kernel leaves
+    int32_t *spill_list2 = nullptr;  // 3D: overflows of the first spill pass
     int32_t *sample_list = nullptr;  // tuning sample (batches)
     int nsample = 0;
     double *xscratch = nullptr;
@@ -510,7 +510,7 @@ vc_status create_common(vc_container *c, const double *xyz, const int64_t *offse
     TRY(dalloc(&c->offs, offs.size()));
     TRY(dalloc(&c->queue, 8));
     TRY(dalloc(&c->spill_list, (size_t)c->n));
-    if (dim == 3 || cells_by_lane(dim, c->n, c->launch.vcap)) TRY(dalloc(&c->spill_list2, (size_t)c->n));
+    if (dim == 3) TRY(dalloc(&c->spill_list2, (size_t)c->n));
     TRY(dalloc(&c->xscratch, (size_t)c->max_waves * c->xscratch_len));
 #undef TRY
     HIP_TRY(hipMemcpyAsync(c->tess, c->htess.data(), c->htess.size() * sizeof(Tess), hipMemcpyHostToDevice, s));
@@ -553,7 +553,7 @@ CellArgs cell_args(const vc_container *c, const vc_result *r)
     A.status = r->status;
     A.spill_list = c->spill_list;
     A.spill_count = c->queue + 2;
-    A.left_list = c->spill_list2;
+    A.left_list = c->rank;
     A.left_queue = c->queue + 6;
     A.left_count = c->queue + 7;
     A.band_queue = c->queue + 3;
