@@ -481,21 +481,18 @@ __device__ __forceinline__ int co_batch(const CellArgs &A, SL<G, S, MAXP, RAD> &
         valid = d2 < lim && !(idx == sh.gs.si && code == kNoShift);
     }
     unsigned long long vm = __builtin_amdgcn_ballot_w64(valid);
-    int width = 64;
+    // radical: whether an empty cell on a coincident particle is a duplicate
+    // or empty depends on which of the two shows first, by G particles at a time
+    int width = RAD && __builtin_amdgcn_ballot_w64(valid && lane >= G && d2 == 0.0) ? G : 64;
+    if (width < 64) vm &= Gw<G>::FULL;
     if (__popcll(vm) > G) {
         do {
             width >>= 1;
             vm &= (1ull << width) - 1;
         } while (width > G && __popcll(vm) > G);
-        valid = valid && lane < width;
+        if (!RAD) valid = valid && lane < width;
     }
-    // radical: whether an empty cell on a coincident particle is a duplicate
-    // or empty depends on which of the two shows first, by G particles at a time
-    if (RAD && (__builtin_amdgcn_ballot_w64(valid && d2 == 0.0) & ~(unsigned long long)Gw<G>::FULL)) {
-        width = G;
-        vm &= Gw<G>::FULL;
-        valid = valid && lane < G;
-    }
+    if (RAD) valid = (vm >> lane) & 1;
     bn = __popcll(vm);
     sh.gs.gc0 = c0 + width;
     if (bn == 0) return PH_BATCH;
