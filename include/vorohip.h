@@ -129,7 +129,8 @@ enum { VC_CELL_OK = 0, VC_CELL_SPILLED = 1, VC_CELL_CAPACITY = 2, VC_CELL_DUPLIC
 
 /* diagnostic counters (VC_F_DIAG) */
 enum {
-    VC_D_CANDIDATES = 0,  /* candidates taken in nearest-first order */
+    VC_D_CANDIDATES = 0,  /* candidates taken (in nearest-first order; 2D with one cell per
+                             lane: in the order of the blocks, so more of them) */
     VC_D_TESTS = 1,       /* plane-side tests (candidates x live vertices) */
     VC_D_CUTS = 2,        /* cuts that removed part of a cell */
     VC_D_NEWV = 3,        /* vertices created */

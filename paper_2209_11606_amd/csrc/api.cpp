@@ -226,7 +226,7 @@ struct Launch {
 // within 1%, 16 +2%, 32 +6%).  In 2D a grab is one or two cells for every group,
 // since its groups take them in turn (79,999 cells: 0.44 ms a step with grabs of
 // eight, 0.53 with nine).  The 2D lane kernel always fills its 64 lanes
-// (100,000 cells: 0.53 ms a step against 0.70 with 24 lanes in use).  A caller's
+// (100,000 cells: 0.37 ms a step against 0.46 with 24 lanes in use).  A caller's
 // chunk is the cells of a group: a wave's grab is that for each of its groups,
 // and by lane, where the wave is one group, that many cells in whole sets of 64
 // (10^6 cells with chunk 64: 9.0 ms a step with 64 for each lane, 1.6 with 64).
@@ -246,12 +246,13 @@ void fit_launch(int64_t ncell, int dim, int per_wave, int &waves, int &chunk)
 
 // 2D sets of this many particles and more are computed one cell per lane, the
 // others eight lanes per cell: a wave of the lane kernel takes long however few
-// cells there are.  Steps by eight lanes and by lane: 20,000 cells 0.41 and 0.44
-// ms, 60,000 0.55 and 0.49, 100,000 0.67 and 0.52, 10^6 3.2 and 1.77; radical
-// 40,000 0.53 and 0.56, 100,000 0.71 and 0.66, 10^6 3.8 and 3.1.  One line for
-// both, since equal radii give the Voronoi cells bit for bit.  The container's
-// size decides, so that a subset's cells are those of the whole set; a vertex
-// capacity asks for the kernel whose slots it limits.
+// cells there are.  Steps by eight lanes and by lane: 10,000 cells 0.21 and 0.27
+// ms, 40,000 0.32 and 0.31, 60,000 0.39 and 0.41, 80,000 0.44 and 0.39, 100,000
+// 0.49 and 0.39, 10^6 3.1 and 1.56; radical 20,000 0.30 and 0.36, 60,000 0.43 and
+// 0.45, 80,000 0.49 and 0.44, 100,000 0.56 and 0.45, 10^6 3.7 and 1.94.  One line
+// for both, since equal radii give the Voronoi cells bit for bit.  The
+// container's size decides, so that a subset's cells are those of the whole
+// set; a vertex capacity asks for the kernel whose slots it limits.
 constexpr int64_t kLaneCells = 80000;
 
 bool cells_by_lane(int dim, int64_t n, int vcap) { return dim == 2 && vcap == 0 && n >= kLaneCells; }
@@ -260,7 +261,7 @@ bool cells_by_lane(int dim, int64_t n, int vcap) { return dim == 2 && vcap == 0 
 // are resident: a wave's first range is fixed by its number, and one that has to
 // wait for a place starts it late (eight lanes a cell, 40,000 cells: 0.41 ms a
 // step with sixteen a compute unit, 0.32 with eight; 60,000 0.47 and 0.38; by
-// lane, 400,000 0.88 with sixteen, 0.85 with twelve).  Twenty waves of the
+// lane, 10^6 1.58 with sixteen, 1.56 with twelve).  Twenty waves of the
 // two-cell 3D form are resident; the four-cell and four-slot forms, at eight,
 // gain nothing from fewer (300,001 cells at four per wave 4.3 ms with sixteen,
 // 5.0 with eight; with four slots the same).

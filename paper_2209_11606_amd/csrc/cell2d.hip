@@ -821,22 +821,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 // the last for its second; when it removes a single vertex, the slots up to the
 // next hole move by one.  A cell that outgrows the ring or searches past the
 // offset list is left to the kernel above, as part of the main pass.  Bound by
-// instruction issue and by the particle loads' latency (457 VALU instructions a
-// cell, VALU busy 56%); periodic 10^6 cells: 1.33 ms where the kernel above
-// takes 2.85.
+// instruction issue and by the particle loads' latency (452 VALU instructions a
+// cell, VALU busy 69%); periodic 10^6 cells: 1.07 ms where the kernel above
+// takes 2.85, and 0.19 for the two or three with a decision in band.
 // ---------------------------------------------------------------------------
 constexpr int kLaneV = 12;
 
 constexpr int kLaneB = 12;  // blocks a lane gathers at once
 // A gather of more particles than this leaves its cell to the other kernel,
 // whose eight lanes share them: a wave waits for its fullest lane (10^6
-// clustered particles, section 3.1, default grid: 69 ms without the limit, 36
-// with 640, 35 with 1,280; 200,000: 16.3, 5.8 and 6.2; by eight lanes alone 39
-// and 7.6).
+// clustered particles, section 3.1, default grid: 97 ms without the limit, 37
+// with 640 and with 1,280; 200,000: 21.3, 6.0 and 6.7; by eight lanes alone 39
+// and 7.8).
 constexpr int kLaneLoad = 640;
 // The wave turns from particles to cuts once the lanes that wait are half as
 // many as those that go on (10^6 periodic cells, step: waiting for all lanes
-// 3.13 ms, half of the lanes 1.79, a third 1.75, a fifth 1.78).
+// 2.76 ms, half of the lanes 1.56, a third 1.56, a fifth 1.57).
 constexpr int kLaneWait = 2;
 
 struct LaneLds {
@@ -914,11 +914,11 @@ __device__ __forceinline__ int lane_next(uint32_t live, int i)
 // is in the exact predicate's band.  It runs them again from the start and
 // decides exactly, each lane with a workspace of its own.  With the decisions
 // in the main pass, one lane at a time, a periodic lattice of 160,000 took 2.69
-// ms a step (eight lanes a cell: 2.11), with the pass 0.80; and without the call
+// ms a step (eight lanes a cell: 2.11), with the pass 0.71; and without the call
 // the main kernel spills nothing (100,000 particles 0.43 -> 0.41 ms, 10^6 with
 // VC_F32_FILTER 2.62 -> 2.07).
-// three waves per SIMD: at four the polygon and a cut's two lines spill (6.8
-// ms a step against 3.1 with every lane waiting), at two 3.2
+// Three waves per SIMD: 10^6 periodic cells 1.56 ms a step, at four, where the
+// polygon and a cut's two lines spill, 1.62, at two 1.79.
 template <bool F32, bool RAD, bool EX>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_cells2d_lane(CellArgs Ain)
 {
