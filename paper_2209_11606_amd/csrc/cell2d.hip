@@ -1072,7 +1072,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
                         nb++;
                     }
                 }
-                nblk += nb;
                 int got = 0;
                 // their particles' ranges, independent loads
 #pragma unroll 4
@@ -1083,11 +1082,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
                     sh.end[k][lane] = e;
                     got += e - s;
                 }
-                nload += got;
                 gcur = gend = 0;
                 if (got > kLaneLoad) {
                     st = ST_CAP;
                     done = true;
+                } else {
+                    nblk += nb;
+                    nload += got;
                 }
             }
             // two particles ahead

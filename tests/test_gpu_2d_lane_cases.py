@@ -102,7 +102,7 @@ def test_dense_blocks_are_left(v):
     x = W.uniform(n, 2, 1.0, 61)
     a, b = run(v, x, [1, 1], [1, 1], grid=[40, 2]), run(v, x, [1, 1], [1, 1], grid=[40, 2], capacity=16)
     same(a, b)
-    assert a["diag"]["cuts"] == b["diag"]["cuts"]
+    assert a["diag"] == b["diag"]  # nothing was loaded for a cell that is left at its first gather
     r = W.rng(62)
     t, d = r.random(n // 2) * 2 * np.pi, 0.01 * np.sqrt(r.random(n // 2))
     x[: n // 2] = np.stack([0.4 + d * np.cos(t), 0.6 + d * np.sin(t)], 1)
